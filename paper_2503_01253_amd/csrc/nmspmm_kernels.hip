@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -191,12 +192,14 @@ int64_t plan_ws_bytes(const Plan &p)
 int stage_nq(int KA, int RS)
 {
     static const int shapes[][2] = {{32, 1}, {32, 2}, {32, 3}, {32, 4}, {32, 8},
-                                    {64, 2}, {64, 4}, {64, 8}, {128, 1}, {128, 2}, {128, 4}};
+                                    {64, 2}, {64, 4}, {64, 8}, {128, 1}, {128, 2}, {128, 4}, {128, 12}};
     int best = 0;
     for (const auto &sh : shapes) {
         // (64, 8) only for whole stages of 32 rows (the deep stages of the
         // 16-wave tiles), never as padding
         if (sh[0] == 64 && sh[1] == 8 && RS != 32) continue;
+        // nor (128, 12): the 16-wave tiles at 12:32
+        if (sh[0] == 128 && sh[1] == 12 && RS != 48) continue;
         if (sh[0] == KA && 4 * sh[1] >= RS && (best == 0 || sh[1] < best)) best = sh[1];
     }
     return best;
@@ -237,32 +240,18 @@ double occupancy_of_grid(const TileInfo &t, int64_t m, int64_t n)
     return (double)tiles / (double)(rounds * slots);
 }
 
-// Tile-shape preference by problem size, from sweeps on MI355X:
+// Tile-shape preference by problem size where no 16-wave tile is taken
+// (pick_split), from sweeps on MI355X:
 //  * m <= 128 (when the streaming kernel does not apply): 16- and 64-row
 //    tiles with split-k, which keep enough workgroups in flight to stream Bc;
 //  * m or n below 1024: the 128 x 256 tile with 32 x 32 MFMAs, else the
 //    128 x 128 tile (enough tiles to fill the chip, with split-k);
-//  * otherwise, at N/M <= 1/2 with V a multiple of 32, a 16-wave tile when
-//    its grid fills the chip in one round (at most 256 tiles, at least three
-//    quarters of the CUs busy): 128 x 512, else (at N/M = 1/2) 256 x 256,
-//    else 128 x 256.  Four waves per SIMD hide the A loads of one wave behind
-//    the MFMAs of the others (4096^3 at 16:32 566 -> 543 us, at 4:32 184 ->
-//    163 us); on grids of several rounds (2048 x 11008) and on split-k grids
-//    the 8-wave tiles measured faster.  At N/M = 1/2 the 128 x 512 tile,
-//    whose stage offsets come in 16-byte reads, measured ahead of 256 x 256
-//    (per-launch events, 4096^3 at 16:32 543.3 -> 530.8 us, 3072 x 4096 x
-//    4096 545 -> 531, 4096 x 2048 x 4096 281.7 -> 275.7, V = 64 547 -> 533);
-//    the 256 x 256 16-wave tile is still tried second.  At N = M (stages of
-//    32 compressed rows) the 16-wave tiles take the place of the 8-wave
-//    ones where they fill one round: 256 x 256 (4096^3 1029.7 -> 1025.5 us;
-//    128 x 512 measured 1038), else 128 x 256 (2048 x 4096 x 4096 564.2 ->
-//    554.7);
 //  * else the 256 x 256 tile for dense-ish levels (N/M >= 1/2) and the
 //    128 x 512 tile with 32 x 32 MFMAs for the sparser ones, unless its grid
 //    would leave more than a quarter of the chip idle in the last wave, where
 //    the 128 x 256 tile with 32 x 32 MFMAs (two workgroups per CU) is tried
 //    first.
-int preferences(int64_t m, int64_t n, int N, int M, int V, const TileInfo **out)
+int preferences(int64_t m, int64_t n, int N, int M, const TileInfo **out)
 {
     int c = 0;
     auto add = [&](const char *name) { out[c++] = tile_by_name(name); };
@@ -273,16 +262,6 @@ int preferences(int64_t m, int64_t n, int N, int M, int V, const TileInfo **out)
     if (m < 1024 || n < 1024) {
         add("128x256m32"); add("128x128"); add("128x512"); add("256x256");
         return c;
-    }
-    if ((2 * N <= M || N == M) && V % 32 == 0) {
-        auto one_round = [&](const char *name) {
-            const TileInfo &t = *tile_by_name(name);
-            const int64_t tiles = ((m + t.BM - 1) / t.BM) * ((n + t.BN - 1) / t.BN);
-            return tiles <= 256 && occupancy_of_grid(t, m, n) >= 0.75;
-        };
-        if (2 * N <= M && one_round("128x512m32w16")) add("128x512m32w16");
-        else if (2 * N >= M && one_round("256x256m32w16")) add("256x256m32w16");
-        else if (one_round("128x256m32w16")) add("128x256m32w16");
     }
     const char *big = 2 * N >= M ? "256x256" : "128x512m32";
     if (occupancy_of_grid(*tile_by_name(big), m, n) < 0.75) add("128x256m32");
@@ -305,6 +284,18 @@ bool prefer_streaming(int64_t m, int64_t k, int N, int M)
 {
     const int64_t w = (k / M) * N;
     return m <= 128 || (m <= 1024 && m * w <= (int64_t(1) << 20));
+}
+
+// Time expected of the streaming kernels above 128 rows, from measured rates:
+// 60 TFLOP/s from 512 rows on at 12:32 and 16:32 (512 x 2048 x 2048 at 12:32
+// 27.5 us, 1024 x 2048 x 2048 52 us), 72 from 1024 rows on at N/M <= 1/4
+// (1024 x 4096 x 4096 at 4:32 60 us), and less on fewer rows (m x k x n: 300 x
+// 4096 x 4096 41 at 16:32 and 36 at 8:32, 600 x 4096 x 11008 at 4:32 57).
+double streaming_us(int64_t m, int64_t n, int64_t k, int N, int M)
+{
+    const bool sparse = 4 * N <= M;
+    const double full = sparse ? 72e6 : 60e6, part = std::sqrt((double)m / (sparse ? 1024 : 512));
+    return 5 + 2.0 * m * n * ((k / M) * N) / (full * std::min(1.0, part));
 }
 
 // Overrides of the dispatch rules, for tuning sweeps and the forced-variant
@@ -558,14 +549,70 @@ bool plan_rowgather(const float *A, const float *Bc, const float *C, int64_t m, 
     return true;
 }
 
+// The 16-wave tile (the split kernel), its stage and its k split for products
+// of more than 128 rows with V a multiple of 32, and the time expected of
+// them; false where none applies.  The estimate, fitted to MI355X times of
+// full grids (one workgroup per CU, so a grid runs in rounds of 256):
+//   rounds * (K steps per split * t + 8 us) + splits > 1: 5 us + splits * bytes of C / 2 TB/s
+// where t, the time of a K step of 16 compressed rows, grows with the columns
+// of A staged for it: 128 x 512 tiles 2.52 / 2.69 / 3.02 / 3.69 us at 16 / 32
+// / 64 / 128 columns, 128 x 256 tiles 1.34 / 1.53 / 1.92 / 2.69.  It ranks what was measured as
+// measured: 1111 x 4192 x 4096 at 16:32 128 x 512 split 3 140 us, split 2
+// 170, 128 x 256 unsplit 182; 2048 x 4096 x 4096 at 8:32 128 x 256 unsplit
+// 131-138, 128 x 512 split 2 147; 300 x 4096 x 4096 at 16:32 128 x 256 split
+// 4 67, unsplit 182, 128 x 512 split 4 88.  (The 256 x 256 tile stages more
+// of A per output and measured behind 128 x 512 at every level, 16:32 371
+// against 337 us, N = M 655 against 626: it is left to TILE.)
+// Stages less than half full of compressed rows (2:32 and below) leave the
+// work to the fp32 instruction's tiles, whose K step is 2 rows.
+struct SplitPick {
+    const TileInfo *tile = nullptr;
+    int KA = 0, NQ = 0;
+    int64_t splits = 1;
+    double us = 0;
+};
+
+bool pick_split(const float *A, const float *Bc, int64_t m, int64_t n, int64_t k, int N, int M, int V, SplitPick &out)
+{
+    if (m <= 128 || k == 0 || V % 32 != 0 || k % 4 != 0 || 128 % M != 0 || !aligned(A, 16) || !aligned(Bc, 16))
+        return false;
+    if (64 * n * 4 >= (int64_t(1) << 31)) return false;   // offsets in a stage of Bc
+    static const struct { const char *name; double t0, t1; } tiles[] = {{"128x512m32w16", 2.35, 0.0105},
+                                                                        {"128x256m32w16", 1.15, 0.0120}};
+    for (const auto &c : tiles) {
+        const TileInfo *tile = tile_by_name(c.name);
+        // (of equal estimates the first: 64 columns before 32, half the barriers,
+        // 4096^3 at 16:32 345 against 360 us)
+        for (int KA : {64, 32, 128}) {
+            if (KA % M != 0) continue;
+            const int RS = (KA / M) * N, nq = stage_nq(KA, RS);
+            const int ks = (nq + 3) / 4;
+            if (nq == 0 || 2 * RS <= 16 * ks || !tile_ok(*tile, 1, KA, nq, k, V)) continue;
+            const int64_t gps = KA / M, stages = (k / M + gps - 1) / gps;
+            const int64_t ntiles = ((m + tile->BM - 1) / tile->BM) * ((n + tile->BN - 1) / tile->BN);
+            if (ntiles > (1 << 24) || stages > INT32_MAX) continue;
+            const double t = c.t0 + c.t1 * KA / ks;
+            for (int64_t s = 1; s <= std::min<int64_t>(8, stages); ++s) {
+                const int64_t rounds = (ntiles * s + 255) / 256;
+                double us = rounds * ((double)((stages + s - 1) / s) * ks * t + 8);
+                if (s > 1) us += 5 + (double)m * n * 4 * s / 2e6;
+                if (!out.tile || us < out.us) out = SplitPick{tile, KA, nq, s, us};
+            }
+        }
+    }
+    return out.tile != nullptr;
+}
+
 Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64_t n, int64_t k,
                int N, int M, int V, const Tuning &t)
 {
     Plan p;
     if (m == 0 || n == 0) return p;
     const char *force_tile = t.tile_or_null();
-    const bool want_skinny =
-        force_tile ? std::strcmp(force_tile, "skinny") == 0 : prefer_streaming(m, k, N, M);
+    SplitPick sp;
+    const bool have_split = !force_tile && t.ka == 0 && t.splits < 1 && pick_split(A, Bc, m, n, k, N, M, V, sp);
+    const bool want_skinny = force_tile ? std::strcmp(force_tile, "skinny") == 0
+                                        : prefer_streaming(m, k, N, M) && !(have_split && sp.us < streaming_us(m, n, k, N, M));
     if (want_skinny) {
         if (t.rg != 0 && plan_rowgather(A, Bc, C, m, n, k, N, M, V, t.rg == 1, t, p)) return p;
         // the PS override (tuning sweeps and tests): 0 never takes the
@@ -616,10 +663,16 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
     }
 
     const TileInfo *cand[8];
-    int nc = preferences(m, n, N, M, V, cand);
+    int nc = preferences(m, n, N, M, cand);
     if (force_tile) {
         const TileInfo *t = tile_by_name(force_tile);
         if (t) { cand[0] = t; nc = 1; }
+    }
+    if (have_split) {
+        cand[0] = sp.tile;
+        nc = 1;
+        ka_deep[0] = sp.KA;
+        nkd = 1;
     }
     // first tile shape (in preference order) that some stage depth fits
     const TileInfo *tile = nullptr;
@@ -639,7 +692,7 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
         const int norder = small ? nks : deep ? nkd : nka;
         for (int i = 0; i < norder && !tile; ++i) {
             const int nq = stage_nq(order[i], (order[i] / M) * N);
-            if (nq != 0 && tile_ok(*cand[j], bv, order[i], nq, k, V)) {
+            if (nq != 0 && (int64_t)16 * nq * n < (int64_t(1) << 31) && tile_ok(*cand[j], bv, order[i], nq, k, V)) {
                 tile = cand[j];
                 KA = order[i];
                 NQ = nq;
@@ -668,6 +721,7 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
         // the split, 2048 x 2816 on 176 tiles 196.5 -> 165.1.
         if (tile->waves == 16) splits = std::max<int64_t>(1, std::min<int64_t>(splits, target / ntiles));
     }
+    if (have_split) splits = sp.splits;
     if (t.splits >= 1) splits = std::min<int64_t>(t.splits, std::max<int64_t>(stages, 1));
 
     // Two column regions where the sparse levels' wide 16-wave tile would

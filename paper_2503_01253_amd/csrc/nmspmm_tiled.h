@@ -112,16 +112,8 @@ struct Shape {
     static constexpr int SLOT_BYTES = A_BYTES + BX_BYTES;
     static constexpr int LDS_BYTES = A_SLOTS * A_BYTES + NSLOT * BX_BYTES;
     // A: chunks of A_RP rows x 32 columns, one per wave at a time, each
-    // thread an (A_RP/8) x 4 block.  32-row chunks, or 16-row ones on the
-    // 16-wave tiles where 32-row chunks would leave three quarters of the
-    // waves without A work: the waves that load then load and store half as
-    // much, and they set the stage's pace.  Measured on MI355X (per-launch
-    // events): 2048 x 4096 x 4096 at 16:32 on 128 x 256 tiles (KA = 32)
-    // 317.4 -> 306.8 us; where 32-row chunks already kept half the waves busy
-    // (4096^3 at 16:32 and 8:32, 2048 x 4096 x 4096 at 8:32) it measured
-    // within -0.3 / +0.5 %.
-    static constexpr int A_CH32 = ((T::BM + 31) / 32) * (KA / 32);
-    static constexpr int A_RP = (T::NT >= 1024 && (4 * A_CH32 <= T::NW || (NQ == 8 && A_CH32 <= T::NW))) ? 16 : 32;
+    // thread an (A_RP/8) x 4 block
+    static constexpr int A_RP = 32;
     static constexpr int A_RL = A_RP / 8;               // rows per thread
     static constexpr int A_CHUNKS = ((T::BM + A_RP - 1) / A_RP) * (KA / 32);
     static constexpr int ACH = (A_CHUNKS + T::NW - 1) / T::NW;
@@ -129,10 +121,7 @@ struct Shape {
     static constexpr int B_LANE = B_FLOATS * 4 / T::NT;
     static constexpr int B_W = B_LANE % 16 == 0 ? 16 : 4;
     static constexpr int B_CNT = B_LANE / B_W;
-    // 16-wave tiles run four waves per SIMD, 128 VGPRs each: one A staging
-    // chunk per wave and at most four quads per stage (more spill)
-    static constexpr bool REGS_OK = T::NT < 1024 || ((NQ <= 4 || (NQ == 8 && A_RP == 16)) && ACH == 1);
-    static constexpr bool FITS = (TWO_A || ONE_A_OK) && REGS_OK && LDS_BYTES <= LDS_CAPACITY &&
+    static constexpr bool FITS = (TWO_A || ONE_A_OK) && LDS_BYTES <= LDS_CAPACITY &&
                                  KA % 32 == 0 &&
                                  T::WN % CG == 0 && RST * QBMAX <= T::NT &&
                                  (B_FLOATS * 4) % T::NT == 0 && B_LANE % 4 == 0 && B_CNT >= 1;
@@ -357,11 +346,7 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_kernel(TiledArgs p)
             if (chunk < S::A_CHUNKS && rbase + A_RL * r8 < BM) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    arvec v;
-                    if constexpr (A_RL == 4)
-                        v = arvec{ra[ch][0][c], ra[ch][1][c], ra[ch][2][c], ra[ch][3][c]};
-                    else
-                        v = arvec{ra[ch][0][c], ra[ch][1][c]};
+                    const arvec v{ra[ch][0][c], ra[ch][1][c], ra[ch][2][c], ra[ch][3][c]};
                     *reinterpret_cast<arvec *>(As + (cbase + 4 * c8 + c) * AST + rbase + A_RL * r8) = v;
                 }
             }

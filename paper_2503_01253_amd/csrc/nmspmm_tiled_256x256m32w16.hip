@@ -1,19 +1,19 @@
-// Instantiations of the tiled kernel for 256 x 256 tiles on the 32x32x2 fp32
-// MFMA, 2 x 8 waves of 128 x 32
-// (16 waves, four per SIMD: while some wait on their loads the others keep the
-// matrix pipe busy; 64 or fewer accumulators per lane fit the 128 VGPRs).
-#include "nmspmm_tiled.h"
+// Instantiations of the split kernel for 256 x 256 tiles, 2 x 8 waves of 128 x 32
+// (16 waves, four per SIMD: while some wait on their loads or split operands
+// the others keep the matrix pipe busy; at most 64 accumulators per lane fit
+// the 128 VGPRs).
+#include "nmspmm_split.h"
 #include "nmspmm_tiles.h"
 
 namespace nmspmm {
 
-using Tile_256x256m32w16 = TileCfg<256, 256, 128, 32, 32>;
+using Tile_256x256m32w16 = SplitTile<256, 256, 128>;
 
 hipError_t launch_tiled_256x256m32w16(int BV, int KA, int NQ, const TiledArgs &a, hipStream_t stream)
 {
-    return launch_tiled_any<Tile_256x256m32w16>(BV, KA, NQ, a, stream);
+    return BV == 1 ? launch_split_any<Tile_256x256m32w16>(KA, NQ, a, stream) : hipErrorInvalidValue;
 }
 
-bool tiled_fits_256x256m32w16(int BV, int KA, int NQ) { return tiled_fits<Tile_256x256m32w16>(BV, KA, NQ); }
+bool tiled_fits_256x256m32w16(int BV, int KA, int NQ) { return split_fits<Tile_256x256m32w16>(BV, KA, NQ); }
 
 }  // namespace nmspmm

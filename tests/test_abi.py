@@ -391,3 +391,18 @@ def test_dispatch_rules_for_tiled_grids():
     # a forced tile, stage depth or split keeps one region
     assert "+cols" not in name(2048, 11008, 4096, 8, 32, 32, tuning={"SPLITS": 1})
     assert nm.nmspmm_workspace_bytes(2048, 11008, 4096, 8, 32, 32) == 0
+
+
+def test_dispatch_rules_for_the_split_kernel():
+    """Host only.  Above 128 rows the 16-wave tiles where V is a multiple of 32
+    and a stage's K steps of 16 rows are more than half full; tile and k split
+    by the estimate of pick_split."""
+    name = nm.nmspmm_kernel_name
+    assert name(4096, 4096, 4096, 16, 32, 32) == "nm_tiled_kernel<128x512m32w16,bv1,ka64,nq8>,split1"
+    assert name(4096, 4096, 4096, 12, 32, 32) == "nm_tiled_kernel<128x512m32w16,bv1,ka128,nq12>,split1"
+    assert name(1111, 4192, 4096, 16, 32, 32).startswith("nm_tiled_kernel<128x512m32w16,") \
+        and name(1111, 4192, 4096, 16, 32, 32).endswith("split3")
+    assert name(2048, 4096, 4096, 8, 32, 32) == "nm_tiled_kernel<128x256m32w16,bv1,ka64,nq4>,split1"
+    assert "w16" not in name(4096, 4096, 4096, 2, 32, 32)      # half-empty K steps: the fp32 tiles
+    assert "w16" not in name(4096, 4096, 4096, 16, 32, 16)     # V = 16
+    assert name(512, 2048, 2048, 12, 32, 32).startswith("nm_skinny_kernel<")
