@@ -184,6 +184,34 @@ def _check_tensors(torch, C, specs):
             raise ValueError(f"{name} has {t.numel()} elements, expected {numel}")
 
 
+def _checked(torch, C, specs):
+    """The device index of C once every tensor of `specs` has passed: each
+    condition of _check_tensors in one expression (a call's host time is of
+    the order of a small product's GPU time), which words the error of the
+    first that does not."""
+    T = torch.Tensor
+    at = C.get_device() if isinstance(C, T) else -1
+    for _, t, dt, numel in specs:
+        if not (isinstance(t, T) and t.dtype is dt and t.get_device() == at and at >= 0 and t.is_contiguous()
+                and t.numel() == numel):
+            _check_tensors(torch, C, specs)
+    return at
+
+
+def _call(torch, at, fn, *args):
+    """fn(*args) with device `at` current."""
+    if torch.cuda.current_device() == at:
+        return fn(*args)
+    with torch.cuda.device(at):
+        return fn(*args)
+
+
+def _raw_stream(torch, at, stream):
+    """The hipStream_t of `stream`, or of torch's current stream on device
+    `at` (read without building a Stream object, which takes 1 us)."""
+    return torch._C._cuda_getCurrentRawStream(at) if stream is None else stream.cuda_stream
+
+
 def nmspmm_run(A, Bc, idx, C, m: int, n: int, k: int, N: int, M: int, V: int, stream=None, tuning=None):
     """C = A * B_pruned on the GPU, asynchronously on ``stream`` (a
     torch.cuda.Stream; default: torch's current stream).  A (m x k), Bc
@@ -226,7 +254,7 @@ def nmspmm_run_ex(A, Bc, idx, C, m: int, n: int, k: int, N: int, M: int, V: int,
     factor; bias an n-element fp32 CUDA tensor or None; act "none", "relu" or
     "gelu").  Tensors and stream as for nmspmm_run; ``tuning`` as there."""
     import torch
-    L = lib()
+    L = _lib or lib()
     w = (k // M) * N if M > 0 else 0
     q = n // V if V > 0 else 0
     specs = [("A", A, torch.float32, m * k), ("Bc", Bc, torch.float32, w * n),
@@ -235,38 +263,25 @@ def nmspmm_run_ex(A, Bc, idx, C, m: int, n: int, k: int, N: int, M: int, V: int,
         specs.append(("bias", bias, torch.float32, n))
     if _workspace is not None:   # any size: too small means no workspace
         specs.append(("workspace", _workspace, torch.uint8, _workspace.numel()))
-    _check_tensors(torch, C, specs)
+    at = _checked(torch, C, specs)
     if act not in ACTS:
         raise ValueError(f"act must be one of {sorted(ACTS)}")
-    if stream is None:
-        stream = torch.cuda.current_stream(C.device)
-    with torch.cuda.device(C.device):
+    raw = _raw_stream(torch, at, stream)
+    shape = (A.data_ptr(), Bc.data_ptr(), idx.data_ptr(), C.data_ptr(), m, n, k, N, M, V)
+    if _name == "nmspmm_run" and not tuning:
+        st = _call(torch, at, L.nmspmm_run, *shape, raw)
+    else:
+        epi = (float(alpha), None if bias is None else bias.data_ptr(), ACTS[act])
+        ws = (None, 0) if _workspace is None else (_workspace.data_ptr(), _workspace.numel())
         if tuning:
-            st = L.nmspmm_run_tuned(A.data_ptr(), Bc.data_ptr(), idx.data_ptr(), C.data_ptr(),
-                                    m, n, k, N, M, V, float(alpha),
-                                    None if bias is None else bias.data_ptr(), ACTS[act],
-                                    None if _workspace is None else _workspace.data_ptr(),
-                                    0 if _workspace is None else _workspace.numel(),
-                                    tuning_string(tuning), stream.cuda_stream)
             _name = "nmspmm_run_tuned"
+            st = _call(torch, at, L.nmspmm_run_tuned, *shape, *epi, *ws, tuning_string(tuning), raw)
         elif _name == "nmspmm_run_noalloc":
-            st = L.nmspmm_run_noalloc(A.data_ptr(), Bc.data_ptr(), idx.data_ptr(), C.data_ptr(),
-                                      m, n, k, N, M, V, float(alpha),
-                                      None if bias is None else bias.data_ptr(), ACTS[act], stream.cuda_stream)
-        elif _name == "nmspmm_run":
-            st = L.nmspmm_run(A.data_ptr(), Bc.data_ptr(), idx.data_ptr(), C.data_ptr(),
-                              m, n, k, N, M, V, stream.cuda_stream)
+            st = _call(torch, at, L.nmspmm_run_noalloc, *shape, *epi, raw)
         elif _name == "nmspmm_run_ws":
-            st = L.nmspmm_run_ws(A.data_ptr(), Bc.data_ptr(), idx.data_ptr(), C.data_ptr(),
-                                 m, n, k, N, M, V, float(alpha),
-                                 None if bias is None else bias.data_ptr(), ACTS[act],
-                                 None if _workspace is None else _workspace.data_ptr(),
-                                 0 if _workspace is None else _workspace.numel(), stream.cuda_stream)
+            st = _call(torch, at, L.nmspmm_run_ws, *shape, *epi, *ws, raw)
         else:
-            st = L.nmspmm_run_ex(A.data_ptr(), Bc.data_ptr(), idx.data_ptr(), C.data_ptr(),
-                                 m, n, k, N, M, V, float(alpha),
-                                 None if bias is None else bias.data_ptr(), ACTS[act],
-                                 stream.cuda_stream)
+            st = _call(torch, at, L.nmspmm_run_ex, *shape, *epi, raw)
     _check(_name, st)
     return C
 
@@ -281,13 +296,10 @@ def nmspmm_compress_device(B_dense, Bc, idx, N: int, M: int, V: int, stream=None
     k, n = B_dense.shape
     w = (k // M) * N if M > 0 else 0
     q = n // V if V > 0 else 0
-    _check_tensors(torch, B_dense, [("B_dense", B_dense, torch.float32, k * n),
-                                    ("Bc", Bc, torch.float32, w * n), ("idx", idx, torch.uint8, w * q)])
-    if stream is None:
-        stream = torch.cuda.current_stream(B_dense.device)
-    with torch.cuda.device(B_dense.device):
-        st = lib().nmspmm_compress_device(B_dense.data_ptr(), k, n, N, M, V, Bc.data_ptr(),
-                                          idx.data_ptr(), stream.cuda_stream)
+    at = _checked(torch, B_dense, [("B_dense", B_dense, torch.float32, k * n),
+                                   ("Bc", Bc, torch.float32, w * n), ("idx", idx, torch.uint8, w * q)])
+    st = _call(torch, at, lib().nmspmm_compress_device, B_dense.data_ptr(), k, n, N, M, V, Bc.data_ptr(),
+               idx.data_ptr(), _raw_stream(torch, at, stream))
     _check("nmspmm_compress_device", st)
     return Bc, idx
 
@@ -303,12 +315,9 @@ def nmspmm_confusion(C_sparse, C_dense, W, stream=None):
     if C_dense.dim() != 2:
         raise ValueError("C_dense must be 2-D")
     m, n = C_dense.shape
-    _check_tensors(torch, W, [("C_sparse", C_sparse, torch.float32, m * n),
-                              ("C_dense", C_dense, torch.float32, m * n), ("W", W, torch.float32, m * n)])
-    if stream is None:
-        stream = torch.cuda.current_stream(W.device)
-    with torch.cuda.device(W.device):
-        st = lib().nmspmm_confusion(C_sparse.data_ptr(), C_dense.data_ptr(), W.data_ptr(), m, n,
-                                    stream.cuda_stream)
+    at = _checked(torch, W, [("C_sparse", C_sparse, torch.float32, m * n),
+                             ("C_dense", C_dense, torch.float32, m * n), ("W", W, torch.float32, m * n)])
+    st = _call(torch, at, lib().nmspmm_confusion, C_sparse.data_ptr(), C_dense.data_ptr(), W.data_ptr(), m, n,
+               _raw_stream(torch, at, stream))
     _check("nmspmm_confusion", st)
     return W

@@ -1300,23 +1300,26 @@ nmspmm_status_t run_impl(const float *A, const float *Bc, const uint8_t *idx, fl
     if (st != NMSPMM_OK || m == 0 || n == 0) return st;
     if (workspace && !aligned(workspace, 256)) return NMSPMM_ERR_UNSUPPORTED;
     int cached = -1;
-    if (pooled) {
-        const Plan pw = make_ws_plan(A, Bc, C, m, n, k, N, M, V, t);
-        const int64_t need = pw.kind == Kind::Gather ? plan_ws_bytes(pw) : 0;
-        if (need > 0 && (!workspace || (uint64_t)need > (uint64_t)ws_bytes) && !capturing(stream)) {
+    // the plan of a call with a workspace; that of a call without differs only
+    // where the former is the direct-gather kernel, which cannot run without
+    Plan p;
+    bool planned = false;
+    if (workspace || pooled) {
+        p = make_ws_plan(A, Bc, C, m, n, k, N, M, V, t);
+        const int64_t need = plan_ws_bytes(p);
+        planned = p.kind != Kind::Gather || (workspace && (uint64_t)need <= (uint64_t)ws_bytes);
+        if (!planned && pooled && !capturing(stream)) {
             void *buf = ws_acquire(stream, (size_t)need, &cached);
             if (buf) {
                 workspace = buf;
                 ws_bytes = (size_t)need;
+                planned = true;
             } else {
                 cached = -1;
             }
         }
     }
-    // with a workspace large enough for it, the plan of nmspmm_workspace_bytes;
-    // otherwise that of a call without one
-    Plan p = workspace ? make_ws_plan(A, Bc, C, m, n, k, N, M, V, t) : make_plan(A, Bc, C, m, n, k, N, M, V, t);
-    if (workspace && (uint64_t)plan_ws_bytes(p) > (uint64_t)ws_bytes) p = make_plan(A, Bc, C, m, n, k, N, M, V, t);
+    if (!planned) p = make_plan(A, Bc, C, m, n, k, N, M, V, t);
     if (p.kind == Kind::None) {
         if (cached >= 0) (void)ws_done(cached, stream);
         return NMSPMM_OK;
