@@ -531,7 +531,12 @@ bool plan_rowgather(const float *A, const float *Bc, const float *C, int64_t m, 
                     int M, int V, bool force, const Tuning &t, Plan &p)
 {
     if (m > 32 || k == 0 || !aligned(A, 4) || !aligned(Bc, 16) || !aligned(C, 4)) return false;
-    if (!force && (m > 4 || n / 32 < 256)) return false;
+    const int64_t strips = n / 32, w = k / M * N;
+    const int kb = rowgather_lds_kb(A, m, k, N, M);
+    const bool staged = kb && (m <= 4 || k > 1024) && (m <= 8 || w >= 512) &&
+                        (strips >= 192 || (strips >= 64 && w <= 512)) &&
+                        (strips <= 256 || kb == 48 || k > 2048 || w >= 1024);
+    if (!force && !staged && (m > 4 || strips < 256)) return false;
     RowGatherCfg c{m <= 16 ? 1 : 2, 2, 8, 4};
     if (t.rgct) c.CT = t.rgct;
     if (t.rgnw) c.NW = t.rgnw;

@@ -1,0 +1,74 @@
+"""The row-gather kernel with A and the offsets in LDS, at its edges, against
+the oracle: both forms (one row by FMA, up to 16 by MFMA), sums that are no
+multiple of a load's rows, k no multiple of a DMA piece, more offsets than one
+pass loads, every LDS size, and where it does not apply."""
+import numpy as np
+import pytest
+
+import oracle
+from nm_workloads import make_inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2503_01253_amd as nm  # noqa: E402
+
+FORCE = {"TILE": "skinny", "RG": 1}
+
+
+def run(A, Bc, idx, shape, offset=0, **ex):
+    m, k, n, N, M, V = shape
+    assert nm.nmspmm_kernel_name(m, n, k, N, M, V, tuning=FORCE).startswith("nm_rowgather_kernel<r16,c32,w8,d4>")
+    store = torch.empty(offset + m * k, device="cuda")
+    dA = store[offset:].view(m, k)
+    dA.copy_(torch.from_numpy(A))
+    C = torch.full((m, n), float("nan"), device="cuda")
+    nm.nmspmm_run_ex(dA, torch.from_numpy(Bc).cuda(), torch.from_numpy(idx).cuda(), C, m, n, k, N, M, V,
+                     tuning=FORCE, **ex)
+    return C.cpu().numpy()
+
+
+# (m, k, n, N, M, V)
+SHAPES = [
+    (1, 32, 32, 4, 32, 32), (1, 776, 512, 3, 8, 32), (1, 8192, 96, 16, 32, 32), (1, 16384, 64, 12, 32, 64),
+    (2, 36, 128, 3, 4, 32), (3, 1000, 128, 5, 8, 32), (4, 8192, 64, 4, 32, 32), (5, 2044, 128, 1, 4, 32),
+    (9, 4096, 64, 32, 32, 32), (16, 2048, 288, 8, 32, 96), (15, 260, 256, 13, 20, 64), (16, 4096, 64, 4, 32, 32),
+]
+
+
+@pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "unaligned"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_exact(shape, offset):
+    m, k, n, N, M, V = shape
+    A, Bp, _ = make_inputs(m, k, n, N, M, V, m + k, "int")
+    Bc, idx = oracle.compress(Bp, N, M, V)
+    ref = oracle.spmm(A, Bc, idx, m, n, k, N, M, V)
+    assert np.array_equal(run(A, Bc, idx, shape, offset).astype(np.float64), ref)
+    bias = np.arange(n, dtype=np.float32) - n // 2
+    C = run(A, Bc, idx, shape, offset, alpha=2.0, bias=torch.from_numpy(bias).cuda(), act="relu")
+    assert np.array_equal(C.astype(np.float64), oracle.epilogue(ref, 2.0, bias, "relu"))
+
+
+@pytest.mark.parametrize("m", [1, 4])
+def test_rows_past_w_gather_zeros(m):
+    """An infinite value of A that no compressed row gathers reaches no sum,
+    though the last load's rows past w multiply by zeros."""
+    shape = _, k, n, N, M, V = m, 96, 128, 3, 32, 32
+    A, Bp, mask = make_inputs(m, k, n, N, M, V, 5, "int")
+    Bc, idx = oracle.compress(Bp, N, M, V)
+    unused = ~mask.any(axis=1)
+    assert unused.any()
+    A[:, unused] = np.inf
+    C = run(A, Bc, idx, shape)
+    assert np.array_equal(C.astype(np.float64), oracle.spmm(A, Bc, idx, m, n, k, N, M, V))
+
+
+def test_default_dispatch():
+    name = nm.nmspmm_kernel_name
+    assert name(8, 8192, 4096, 4, 32, 32).startswith("nm_rowgather_kernel<r16,")     # A fits, 256 strips
+    assert name(1, 2048, 2048, 8, 32, 32).startswith("nm_rowgather_kernel<r16,")     # 64 strips of w = 512
+    assert name(4, 4096, 8192, 8, 32, 32).startswith("nm_skinny_kernel<")            # 128 strips of w = 2048
+    assert name(16, 11008, 2048, 8, 32, 32).startswith("nm_skinny_kernel<")          # short k, two rounds
