@@ -109,8 +109,12 @@ NMSPMM_API nmspmm_status_t nmspmm_compress(const float *B_dense, int64_t k, int6
  * kernels that take none instead (named by
  * nmspmm_kernel_name_tuned with with_workspace = 0), as it does for every
  * other shape.  Callers that cannot allocate at all use nmspmm_run_noalloc.  m == 0 or n == 0 returns NMSPMM_OK without a launch;
- * k == 0 writes zeros to C.  Summation order: fp32 MFMA accumulation in an
- * order fixed by the kernel variant; when the variant splits k across
+ * k == 0 writes zeros to C.  Arithmetic: fp32 products and fp32 sums.  (The
+ * 16-wave tiles form the products on the bf16 matrix instruction from three
+ * bf16 parts of each operand that hold all its 24 bits, |x| >= 2^-110; sums
+ * that are infinite, NaN or below 2^-96 are formed in plain fp32.  Their
+ * error against fp64 is below that of the fp32 matrix instruction.)
+ * Summation order: fp32 accumulation in an order fixed by the kernel variant; when the variant splits k across
  * workgroups through atomics (the name from nmspmm_kernel_name ends in
  * "+zero,splitS" with S > 1) the partial tiles are added to C with fp32
  * atomics, so the last bits of C may differ between runs; through the

@@ -586,8 +586,8 @@ bool pick_split(const float *A, const float *Bc, int64_t m, int64_t n, int64_t k
                                                                         {"128x256m32w16", 1.15, 0.0120}};
     for (const auto &c : tiles) {
         const TileInfo *tile = tile_by_name(c.name);
-        // (of equal estimates the first: 64 columns before 32, half the barriers,
-        // 4096^3 at 16:32 345 against 360 us)
+        // a barrier for every K step of 32 columns costs 5 %: 4096^3 at 16:32 360
+        // us against 345 in stages of two, 1111 x 4192 x 4096 150 against 140
         for (int KA : {64, 32, 128}) {
             if (KA % M != 0) continue;
             const int RS = (KA / M) * N, nq = stage_nq(KA, RS);
@@ -596,7 +596,7 @@ bool pick_split(const float *A, const float *Bc, int64_t m, int64_t n, int64_t k
             const int64_t gps = KA / M, stages = (k / M + gps - 1) / gps;
             const int64_t ntiles = ((m + tile->BM - 1) / tile->BM) * ((n + tile->BN - 1) / tile->BN);
             if (ntiles > (1 << 24) || stages > INT32_MAX) continue;
-            const double t = c.t0 + c.t1 * KA / ks;
+            const double t = (c.t0 + c.t1 * KA / ks) * (KA == 32 && ks == 1 ? 1.05 : 1.0);
             for (int64_t s = 1; s <= std::min<int64_t>(8, stages); ++s) {
                 const int64_t rounds = (ntiles * s + 255) / 256;
                 double us = rounds * ((double)((stages + s - 1) / s) * ks * t + 8);
@@ -652,10 +652,9 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
             if (KA % M == 0 && (KA / M) * N < min_rows) order[cnt++] = KA;
         return cnt;
     };
-    // The 16-wave tiles take stages of exactly 32 compressed rows where
-    // those fit (their 16-row A chunks leave the registers for them): half as
-    // many barriers per MFMA.  Measured (per-launch events): 2048 x 4096 x 4096 at
-    // 16:32 on 128 x 256 tiles 300.2 -> 292.0 us (KA = 64).
+    // A forced 16-wave tile takes stages of exactly 32 compressed rows where
+    // those fit, half as many barriers per MFMA; pick_split names the stage
+    // of the others.
     int ka_order[3], ka_small[3], ka_deep[4];
     int nka = ka_list(16, ka_order), nks = ka_list(8, ka_small), nkd = 0;
     for (int KA : {32, 64, 128})   // a whole stage of 32 rows, no padding, then the usual order
@@ -719,11 +718,8 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
     int64_t splits = 1;
     if (ntiles < target && stages > 1) {
         splits = std::min<int64_t>({(target + ntiles - 1) / ntiles, stages, 32});
-        // The 16-wave tiles run one workgroup per CU: a split that overflows
-        // one round leaves a partial second one, so they split only into
-        // whole rounds.  Measured on MI355X at 8:32, k = 4096 (graph replay):
-        // 1536 x 4096 on 192 tiles of 128 x 256 199.6 -> 165.0 us without
-        // the split, 2048 x 2816 on 176 tiles 196.5 -> 165.1.
+        // A forced 16-wave tile (one workgroup per CU) splits only into whole
+        // rounds of the chip.
         if (tile->waves == 16) splits = std::max<int64_t>(1, std::min<int64_t>(splits, target / ntiles));
     }
     if (have_split) splits = sp.splits;
@@ -733,12 +729,9 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
     // need more than one round but the rest fits in one: whole 128 x 512
     // column tiles for one round, then the remaining columns as one round of
     // the 128 x 256 16-wave tile, a second launch, neither split.  Measured
-    // on MI355X (2048 x 11008 x 4096 at 8:32, per-launch events): the two
-    // regions alone take 284.9 us (2048 x 8192) and 165.1 us (2048 x 2816),
-    // against 474.8 us for the 128 x 256 8-wave tile over the whole grid
-    // (688 tiles, two per CU); at 4:32 260.3 against 362.8.  At 12:32 and
-    // 16:32 the 8-wave tile stays ahead (670 against 686 us, 832 against 858
-    // for the two regions timed alone).
+    // on MI355X (m x k x n 2048 x 4096 x 11008): at 8:32 316 us, where whole
+    // rounds of one tile take 2 x 194 (128 x 512) or 3 x 133 (128 x 256); at
+    // 4:32 200.
     if (!force_tile && !ka_force && t.splits < 1 && 4 * N <= M && V % 32 == 0 && m >= 1024 && n >= 1024) {
         const TileInfo *big = tile_by_name("128x512m32w16"), *rest = tile_by_name("128x256m32w16");
         const int64_t tm = (m + big->BM - 1) / big->BM;
