@@ -535,7 +535,8 @@ bool plan_rowgather(const float *A, const float *Bc, const float *C, int64_t m, 
     const int kb = rowgather_lds_kb(A, m, k, N, M);
     const bool staged = kb && (m <= 4 || k > 1024) && (m <= 8 || w >= 512) &&
                         (strips >= 192 || (strips >= 64 && w <= 512)) &&
-                        (strips <= 256 || kb == 48 || k > 2048 || w >= 1024);
+                        (strips <= 256 || (w >= 448 && (kb == 48 || k > 2048 || w >= 1024) &&
+                                           (kb < 150 || w <= 2048 || strips % 256 == 0 || strips % 256 >= 48)));
     if (!force && !staged && (m > 4 || strips < 256)) return false;
     RowGatherCfg c{m <= 16 ? 1 : 2, 2, 8, 4};
     if (t.rgct) c.CT = t.rgct;
@@ -597,7 +598,7 @@ bool pick_split(const float *A, const float *Bc, int64_t m, int64_t n, int64_t k
             const int64_t ntiles = ((m + tile->BM - 1) / tile->BM) * ((n + tile->BN - 1) / tile->BN);
             if (ntiles > (1 << 24) || stages > INT32_MAX) continue;
             const double t = (c.t0 + c.t1 * KA / ks) * (KA == 32 && ks == 1 ? 1.05 : 1.0);
-            for (int64_t s = 1; s <= std::min<int64_t>(8, stages); ++s) {
+            for (int64_t s = 1; s <= std::min<int64_t>(32, stages); ++s) {
                 const int64_t rounds = (ntiles * s + 255) / 256;
                 double us = rounds * ((double)((stages + s - 1) / s) * ks * t + 8);
                 if (s > 1) us += 5 + (double)m * n * 4 * s / 2e6;
