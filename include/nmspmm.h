@@ -109,11 +109,15 @@ NMSPMM_API nmspmm_status_t nmspmm_compress(const float *B_dense, int64_t k, int6
  * kernels that take none instead (named by
  * nmspmm_kernel_name_tuned with with_workspace = 0), as it does for every
  * other shape.  Callers that cannot allocate at all use nmspmm_run_noalloc.  m == 0 or n == 0 returns NMSPMM_OK without a launch;
- * k == 0 writes zeros to C.  Arithmetic: fp32 products and fp32 sums.  (The
+ * k == 0 writes zeros to C.  Arithmetic: fp32 products and fp32 sums.  The
  * 16-wave tiles form the products on the bf16 matrix instruction from three
- * bf16 parts of each operand that hold all its 24 bits, |x| >= 2^-110; sums
- * that are infinite, NaN or below 2^-96 are formed in plain fp32.  Their
- * error against fp64 is below that of the fp32 matrix instruction.)
+ * bf16 parts of each operand, which hold all 24 bits of an operand of 2^-110
+ * or more.  A tile of C is formed on the fp32 matrix instruction instead where
+ * one of its sums is infinite, NaN or non-zero below 2^-96, or where operands
+ * below 2^-110 meet so large ones that they could move a sum by more than
+ * 2^-26 of itself; such a tile takes up to four times as long (4096^3 at
+ * 16:32: 342 us, 1230 with a NaN in A).  On operands of ordinary size the error
+ * against fp64 is below that of the fp32 matrix instruction.
  * Summation order: fp32 accumulation in an order fixed by the kernel variant; when the variant splits k across
  * workgroups through atomics (the name from nmspmm_kernel_name ends in
  * "+zero,splitS" with S > 1) the partial tiles are added to C with fp32

@@ -19,10 +19,10 @@
 // the place of eight of 64 cycles.
 //
 // An operand that is infinite or NaN, or that rounds to an infinite bf16, has
-// no such split (its further parts are NaN), and a sum below 2^-96 may come
-// from operands too small for one: a wave whose sums are not all zero or of
-// ordinary size forms those sums again in plain fp32 from A and Bc
-// (resum_terms), so that such inputs give what fp32 arithmetic gives.
+// no such split (its further parts are NaN), and one below 2^-110 an inexact
+// one.  A workgroup whose sums the split cannot vouch for forms its tile again
+// on the fp32 instruction, so that such inputs give what that instruction
+// gives (see the end of the kernel for the conditions).
 //
 // One workgroup of 16 waves owns a BM x BN tile of C (and, with split-k, one
 // slice of the k range), each wave WM x 32 of it inside one column block.  It
@@ -39,8 +39,10 @@
 //         instruction beyond the read itself.
 //   Bc  : straight from global memory into registers (8 rows of its column
 //         per lane, one K step ahead), split there: no LDS traffic.
-//   X_s : the stage's offset bytes, buffer->LDS DMA, a zero-extended dword
-//         each.
+//   X_s : for each of the stage's compressed rows and the tile's column blocks
+//         the place in A_s of the plane row it gathers, formed from the offset
+//         byte by the thread that loads it (by the readers, 18 instructions a
+//         K step and four registers more).
 // LDS rows are 16-output-row granules of 32 bytes; granule g of plane row c
 // lies at position g ^ swz(c), which spreads both the transposed reads (four
 // plane rows at one granule) and the writes (one granule of many plane rows)
@@ -109,28 +111,165 @@ struct SplitShape {
 // Position, in granules, that granule g of plane row c is stored at: g ^ swz(c).
 __device__ __forceinline__ int swz(int c) { return (2 * (c & 3) + (c >> 2)) & 7; }
 
-// A sum the split cannot vouch for: infinite, NaN, or non-zero below 2^-96.
-__device__ __forceinline__ bool split_unsure(float x)
-{
-    const float a = __builtin_fabsf(x);
-    return !(a <= 3.4028234663852886e38f) || (a < 0x1p-96f && a != 0.f);
-}
+// The bits of x without its sign, shifted up.  (A function: clang's
+// __builtin_bit_cast of an element of a vector takes the first one.)
+__device__ __forceinline__ uint32_t unsigned_bits(float x) { return __builtin_bit_cast(uint32_t, x) << 1; }
 
-// The 16 sums of one 32 x 32 MFMA tile of this lane (rows row0 + 8*(e/4) + e%4,
-// one column) over compressed rows [u0, u1), in plain fp32 in row order.
-__device__ inline void resum_terms(float (&sum)[16], const TiledArgs &p, int64_t row0, int64_t col, int64_t u0,
-                                   int64_t u1)
+// An order (of unsigned values) that puts the operands that do not split last:
+// from 2^-110 on by size, then infinities and NaN, then zero (SPLIT_ZERO),
+// then the non-zero ones below 2^-110.
+constexpr uint32_t SPLIT_MIN = 2 * 0x08800000u;   // unsigned_bits of 2^-110
+constexpr uint32_t SPLIT_ZERO = 0u - SPLIT_MIN;
+__device__ __forceinline__ uint32_t split_rank(float x) { return unsigned_bits(x) - SPLIT_MIN; }
+
+// What follows the stages: whether the split can vouch for every sum of the
+// workgroup's tile, and if not, the tile again on v_mfma_f32_32x32x2_f32, into
+// the same accumulators.  `tiny`: this wave split a non-zero operand below
+// 2^-110.
+//
+// Again, where a sum is infinite, NaN, or non-zero below 2^-96 (part products
+// may be subnormal there).  An operand below 2^-110 is off by at most 2^-134
+// in its three parts, a sum of R terms therefore by R * 2^-133 * top, top the
+// largest operand: below 2^-26 of a sum that is at least R * 2^-107 * top.  So
+// where an operand was tiny, A and Bc are searched for the largest, and the
+// tile is formed again if a sum is below that.
+// Measured on MI355X: the watch (12 instructions for 8 operands) and this cost
+// 1-4 % (4096^3 at 16:32 338 -> 342 us, 4:32 122 -> 126, 600 x 4096 x 4096 at
+// 16:32 88 -> 92).  4096^3 at 16:32 takes 435 with a few operands of 1e-39 in
+// Bc, 1230 with a NaN in A, 1240 with every sum below 2^-96 (sums formed again
+// one by one from memory: 1720 and 6080; the fp32 tiles: 550).
+//
+// Everything is formed anew from laundered copies of the kernel's arguments
+// and ids, and the accumulators are gone through before it is, so that nothing
+// of this takes a register of the kernel's loop.
+template <class T, int KA, int KS>
+__device__ __forceinline__ void split_check(f32x16 (&acc)[T::NRT], unsigned char *lds, uint32_t tiny)
 {
-    const int64_t q = p.n / p.V, b = col / p.V;
+    using S = SplitShape<T, KA, KS>;
+    constexpr int BM = T::BM, BN = T::BN, WM = T::WM, NRT = T::NRT, QBMAX = T::QBMAX, NT = T::NT;
+    typedef const __attribute__((address_space(4))) TiledArgs *args_ptr;
+    args_ptr p = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    int pid = blockIdx.x, tid = threadIdx.x;
+    asm volatile("" : "+s"(p), "+s"(pid), "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    uint32_t *word = reinterpret_cast<uint32_t *>(lds);
+    auto any_wave = [&](uint32_t bits) {   // OR of a wave-uniform value over the workgroup
+        if (lane == 0) word[wave] = bits;
+        lds_sync();
+        const uint32_t x = word[lane % T::NW];
+        return (__any(x & 1) ? 1u : 0u) | (__any(x & 2) ? 2u : 0u);
+    };
+    // of this lane's sums the least non-zero one, without its sign, and the
+    // largest ones of either sign: five instructions for two sums
+    uint32_t lo = ~0u, minus = 0;
+    int plus = 0;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) sum[e] = 0.f;
-    for (int64_t u = u0; u < u1; ++u) {
-        const int64_t c = u / p.N * p.M + min((int)p.idx[u * q + b], p.M - 1);
-        const float bv = p.Bc[u * p.n + col];
+    for (int t = 0; t < NRT; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int64_t row = min64(row0 + 8 * (e / 4) + e % 4, p.m - 1);
-            sum[e] = fmaf(p.A[row * p.k + c], bv, sum[e]);
+            const float x = acc[t][e];
+            lo = min(lo, unsigned_bits(x) - 1u);
+            plus = max(plus, __builtin_bit_cast(int, x));
+            minus = max(minus, __builtin_bit_cast(uint32_t, x));
+        }
+    const bool unsure = lo < 2 * 0x0f800000u - 1u || plus >= 0x7f800000 || minus >= 0xff800000u;
+    uint32_t again = any_wave((__any(unsure) ? 1u : 0u) | tiny << 1);
+    if (again == 0 || NMSPMM_POISON_LDS) return;
+    __builtin_amdgcn_sched_barrier(0);
+
+    const int64_t m = p->m, n = p->n, k = p->k;
+    const int N = p->N, M = p->M, V = p->V, RS = p->RS;
+    int tm, tn, split;
+    map_tile(pid, (int)gridDim.x, p->tiles_m, p->tiles_n, tm, tn, split);
+    const int64_t row0 = (int64_t)tm * BM, col0 = p->col_begin + (int64_t)tn * BN;
+    const int64_t w = (k / M) * N, q = n / V;
+    const int sps = (p->stages + p->splits - 1) / p->splits;
+    const int s_begin = split * sps, s_end = min(p->stages, s_begin + sps);
+    const int wm = wave / QBMAX, wn = wave % QBMAX, r = lane & 31, half = lane >> 5;
+    const int64_t col = col0 + wn * 32 + r;
+    const float *A = p->A, *Bc = p->Bc;
+
+    if (again == 2) {
+        const int64_t u0 = (int64_t)s_begin * RS, u1 = min64((int64_t)s_end * RS, w);
+        const int64_t k0 = (int64_t)s_begin * KA, k1 = min64((int64_t)s_end * KA, k);
+        uint32_t least = ~0u;
+#pragma unroll
+        for (int t = 0; t < NRT; ++t) {
+            asm volatile("" : "+v"(acc[t]));   // a new value: the bits formed above are not kept for this
+#pragma unroll
+            for (int e = 0; e < 16; ++e) least = min(least, unsigned_bits(acc[t][e]));
+        }
+        float top = 0.f;
+        // 16-byte pieces of `rows` rows of `src`, several a thread at a time
+        auto search = [&](const float *src, int64_t rows, int64_t cols, int64_t stride) {
+            constexpr int BATCH = 8 / NRT;
+            const uint32_t c4 = (uint32_t)(cols / 4);
+            const int64_t pieces = rows * c4;
+#pragma unroll 1
+            for (int64_t f0 = tid; f0 < pieces; f0 += NT * BATCH) {
+                f32x4 v[BATCH];   // (the last piece again in place of those past it)
+#pragma unroll
+                for (int y = 0; y < BATCH; ++y) {
+                    const uint32_t f = (uint32_t)min64(f0 + NT * y, pieces - 1), row = f / c4;
+                    v[y] = *reinterpret_cast<const f32x4 *>(src + row * stride + 4 * (f - row * c4));
+                }
+#pragma unroll
+                for (int y = 0; y < BATCH; ++y)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) top = fmaxf(top, __builtin_fabsf(v[y][x]));
+            }
+        };
+        search(A + row0 * k + k0, min64(BM, m - row0), k1 - k0, k);
+        search(Bc + u0 * n + col0, u1 - u0, min64(BN, n - col0), n);
+        lds_sync();
+        if (tid == 0) word[0] = 0;
+        lds_sync();
+        atomicMax(word, __builtin_bit_cast(uint32_t, top));
+        lds_sync();
+        const float bound = (float)(u1 - u0) * 0x1p-107f * __builtin_bit_cast(float, word[0]);
+        lds_sync();
+        if (any_wave(__any(least < unsigned_bits(bound)) ? 1u : 0u) == 0) return;
+    }
+
+    // Stages of KA columns of A, as it is, k-major, in one LDS slot, and of the
+    // offset bytes; a lane reads its rows of Bc from memory.
+    float *A_s = reinterpret_cast<float *>(lds);
+    int *X_s = reinterpret_cast<int *>(lds + S::A_BYTES);
+    const int QB = BN >= V ? BN / V : 1, blk = (int)(min64(col, n - 1) / V - col0 / V);
+#pragma unroll
+    for (int t = 0; t < NRT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+#pragma unroll 1
+    for (int s = s_begin; s < s_end; ++s) {
+        lds_sync();
+#pragma unroll 1
+        for (int i = tid; i < BM * KA / 4; i += NT) {
+            const int row = i / (KA / 4), c = i % (KA / 4) * 4;
+            const int64_t kc = (int64_t)s * KA + c;
+            const f32x4 v = row0 + row < m && kc < k ? *reinterpret_cast<const f32x4 *>(A + (row0 + row) * k + kc)
+                                                     : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int x = 0; x < 4; ++x) A_s[(c + x) * BM + row] = v[x];
+        }
+        if (tid < S::X_ENTRIES) {
+            const int64_t u = (int64_t)s * RS + tid / QBMAX, b = col0 / V + tid % QBMAX;
+            X_s[tid] = tid / QBMAX < RS && u < w && tid % QBMAX < QB && b < q ? p->idx[u * q + b] : 0;
+        }
+        lds_sync();
+        const int nu = (int)min64(RS, w - (int64_t)s * RS);
+#pragma unroll 1
+        for (int y = 0; y < nu; y += 2) {   // two compressed rows, one per half wave
+            const int i = y + half, j = min(i, nu - 1);
+            const int c = j / N * M + min(X_s[j * QBMAX + blk], M - 1);
+            const float bv = i < nu && col < n ? Bc[((int64_t)s * RS + i) * n + col] : 0.f;
+#pragma unroll
+            for (int t = 0; t < NRT; ++t) {
+                // (a row past the last one must not bring an infinity of A to a zero)
+                const float av = i < nu ? A_s[c * BM + wm * WM + 32 * t + r] : 0.f;
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[t], 0, 0, 0);
+            }
         }
     }
 }
@@ -186,6 +325,8 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
                 ra[t] = __builtin_bit_cast(cvec, __builtin_amdgcn_raw_buffer_load_b64(a_rsrc, (int)off, (int)(t * k * 4), 0));
         }
     };
+    uint32_t tiny = 0;   // set once this wave has split a non-zero operand below 2^-110
+    auto watch = [&](uint32_t rank) { tiny |= __any(rank > SPLIT_ZERO) ? 1u : 0u; };
     const int a_dst = ac * STRIDE + 2 * ar, a_swz = (2 * (ac & 3) + (ac >> 2)) << 5;
     auto store_a = [&](int slot) {
         unsigned char *As = lds + (S::TWO_A ? slot * S::A_BYTES : 0);
@@ -193,6 +334,12 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
         // then formed here and not kept in registers through the loop
         int d0 = a_dst, sw = a_swz;
         asm volatile("" : "+v"(d0), "+v"(sw));
+        uint32_t rank = 0;
+#pragma unroll
+        for (int t = 0; t < TR; ++t)
+#pragma unroll
+            for (int c = 0; c < TC; ++c) rank = max(rank, split_rank(ra[t][c]));
+        watch(rank);
 #pragma unroll
         for (int c = 0; c < TC; ++c) {
             // swz(ac + c): ac is a multiple of TC, so ac & 3 plus c stays below 4
@@ -211,10 +358,14 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
         }
     };
 
-    // ---- D offsets: global -> register -> LDS, entry u * QBMAX + block ----
+    // ---- D offsets: global -> register -> LDS, entry u * QBMAX + block: where
+    // the plane row of the column of A that compressed row u gathers lies ----
+    const int gps = KA / M;
     const int x_u = tid / QBMAX, x_b = tid % QBMAX;
     const bool x_ok = tid < S::X_ENTRIES && x_u < RS && x_b < QB && b_first + x_b < q;
     const uint32_t x_off = (uint32_t)(x_u * q + b_first + x_b);
+    // padding rows (>= RS, zero in Bc) gather the last window's first column
+    const int x_window = min(x_u / N, gps - 1) * M;
     int rx = 0;
     auto load_x = [&](int s, bool valid) {
         const int64_t u0 = (int64_t)s * RS;
@@ -224,7 +375,8 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
     };
     auto x_area = [&](int slot) { return reinterpret_cast<int *>(lds + S::A_SLOTS * S::A_BYTES + slot * S::X_BYTES); };
     auto store_x = [&](int slot) {
-        if (tid < S::X_ENTRIES) x_area(slot)[tid] = rx;
+        const int c = x_window + min(rx, M - 1);
+        if (tid < S::X_ENTRIES) x_area(slot)[tid] = c * STRIDE + (swz(c) << 5);
     };
 
     // ---- Bc: 8 rows of this lane's column per K step, straight to registers ----
@@ -239,23 +391,19 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
             rb[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)b_off, (int)((16 * ks + j) * n * 4), 0));
     };
 
+    // (1 in the places outside C, which split_check then takes for ordinary sums)
     f32x16 acc[NRT];
 #pragma unroll
     for (int t = 0; t < NRT; ++t)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+        for (int e = 0; e < 16; ++e)
+            acc[t][e] = col_ok && wm * WM + 32 * t + 8 * (e / 4) + 4 * half + e % 4 < rows_valid ? 0.f : 1.f;
 
     // Lane l of a transposed read addresses piece l%4 (four output rows) of
     // granule l/16%2 of the plane row of compressed row 16*ks + 8*(l/32) +
     // l%16/4, the second read that of the row 4 further on.
-    const int gps = KA / M, tu = 8 * half + ((lane >> 2) & 3);
+    const int tu = 8 * half + ((lane >> 2) & 3);
     const int t_row = (wm * WM + 16 * ((lane >> 4) & 1)) * 2 + 8 * (lane & 3);
-    int window[KS][2];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        // padding rows (>= RS, zero in Bc) address the last window's columns
-        for (int x = 0; x < 2; ++x) window[ks][x] = min((16 * ks + tu + 4 * x) / N, gps - 1) * M;
 
     if (nst > 0) {
         load_x(s_begin, true);
@@ -283,11 +431,11 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
         for (int ks = 0; ks < KS; ++ks) {
             const lds_u8 *at[2];
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const int d = x_area(cur)[(16 * ks + tu + 4 * x) * QBMAX + blk];
-                const int c = window[ks][x] + min(d, M - 1);
-                at[x] = As + c * STRIDE + (t_row ^ (swz(c) << 5));
-            }
+            for (int x = 0; x < 2; ++x) at[x] = As + (x_area(cur)[(16 * ks + tu + 4 * x) * QBMAX + blk] ^ t_row);
+            uint32_t rank = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) rank = max(rank, split_rank(rb[j]));
+            watch(rank);
             u32x4 bp[3];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -336,40 +484,27 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
         lds_sync();
     }
 
-    // ---- epilogue: element e of MFMA tile t is row 32*t + 8*(e/4) + 4*half +
-    // e%4 of the wave's rows, column `col` ----
-    // the lane's place again, from a copy of the lane id the compiler takes for
-    // another value: what follows is then not kept in registers through the loop
+    // ---- the sums the split cannot vouch for, then the epilogue ----
+    // (the lds areas are free: the last stage ended with a barrier)
+    split_check<T, KA, KS>(acc, lds, tiny);
+    // element e of MFMA tile t is row 32*t + 8*(e/4) + 4*half + e%4 of the
+    // wave's rows, column `col`.  The lane's place again, from a copy of the
+    // lane id the compiler takes for another value: what follows is then not
+    // kept in registers through the loop
     int elane = lane;
     asm volatile("" : "+v"(elane));
     const int64_t col = col0 + wn * 32 + (elane & 31);
     const int64_t wrow = row0 + wm * WM + 4 * (elane >> 5);
-    auto put = [&](int64_t row, float v) {
-        if (row >= m || col >= n) return;
-        float *dst = p.C + row * n + col;
-        if (p.splits == 1) *dst = apply_epilogue(p.epi, v, col);
-        else unsafeAtomicAdd(dst, v);
-    };
-    uint32_t unsure[NRT];
 #pragma unroll
-    for (int t = 0; t < NRT; ++t) {
-        unsure[t] = 0;
+    for (int t = 0; t < NRT; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            if (!NMSPMM_POISON_LDS && split_unsure(acc[t][e])) unsure[t] |= 1u << e;
-            else put(wrow + 32 * t + 8 * (e / 4) + e % 4, acc[t][e]);
+            const int64_t row = wrow + 32 * t + 8 * (e / 4) + e % 4;
+            if (row >= m || col >= n) continue;
+            float *dst = p.C + row * n + col;
+            if (p.splits == 1) *dst = apply_epilogue(p.epi, acc[t][e], col);
+            else unsafeAtomicAdd(dst, acc[t][e]);
         }
-    }
-#pragma unroll
-    for (int t = 0; t < NRT; ++t) {
-        if (!__any(unsure[t] != 0 && col < n)) continue;
-        float sum[16];
-        const int64_t u0 = min64((int64_t)s_begin * RS, w), u1 = min64((int64_t)s_end * RS, w);
-        resum_terms(sum, p, wrow + 32 * t, min64(col, n - 1), u0, u1);
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-            if (unsure[t] >> e & 1) put(wrow + 32 * t + 8 * (e / 4) + e % 4, sum[e]);
-    }
 }
 
 // Host-side launcher of one instantiation.

@@ -100,3 +100,47 @@ def test_error_no_larger_than_the_fp32_instruction(shape, dist):
 
     split, fp32 = err("128x512m32w16"), err("128x256m32")
     assert split <= 1.05 * fp32, (split, fp32)
+
+
+# sizes of the operands of A and of Bc: none of these A (or, exchanged, Bc) has
+# three exact bf16 parts, though the sums are of ordinary size; the third ends
+# in sums of which every product would be zero
+TINY = [(2.0 ** -126, 2.0 ** 40), (1e-40, 1e35), (1e-42, 1e38), (1e-37, 1e12), (1e-41, 1e15)]
+
+
+@pytest.mark.parametrize("exchanged", [False, True])
+@pytest.mark.parametrize("tile", ["128x512m32w16", "128x256m32w16"])
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("sizes", TINY, ids=lambda s: f"{s[0]:.0e}x{s[1]:.0e}")
+def test_tiny_operands_beside_large_ones(sizes, splits, tile, exchanged):
+    """fp32's bound for a sum of w products: w roundings of 2^-24."""
+    shape = m, k, n, N, M, V = 140, 256, 288, 16, 32, 32
+    a, b = sizes[::-1] if exchanged else sizes
+    rng = np.random.default_rng(5)
+    A = (rng.uniform(-1, 1, (m, k)) * a).astype(np.float32)
+    _, Bc, idx = inputs(shape, 5, "uniform")
+    Bc = (Bc.astype(np.float64) * b).astype(np.float32)
+    C = run(A, Bc, idx, shape, {"TILE": tile, "SPLITS": splits})
+    w = Bc.shape[0]
+    ref, bound = oracle.spmm(A, Bc, idx, m, n, k, N, M, V), oracle.bound(A, Bc, idx, m, n, k, N, M, V)
+    assert np.abs(ref).max() > 2.0 ** -96
+    assert np.all(np.abs(C - ref) <= w * 2.0 ** -24 * bound + 2.0 ** -149 * w)
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("huge", [1.0, 1e37])
+def test_tiny_operands_among_ordinary_ones(huge, splits):
+    """One column of A of 1e-40, rows of zeros, and (1e37) one row of Bc that
+    makes the tiny operands count: 2^-134 * 1e37 is 5e-4, the sums are 1e-3."""
+    shape = m, k, n, N, M, V = 300, 256, 544, 32, 32, 32
+    A, Bc, idx = inputs(shape, 9, "uniform")
+    A *= np.float32(1e-3)
+    A[:, 37] = np.float32(1e-40) * A[:, 37] / np.abs(A[:, 37]).max()
+    Bc[37] *= np.float32(huge)
+    A[130:150] = 0
+    Bc[:, 64:70] = 0
+    C = run(A, Bc, idx, shape, {"TILE": "128x512m32w16", "SPLITS": splits})
+    w = Bc.shape[0]
+    ref, bound = oracle.spmm(A, Bc, idx, m, n, k, N, M, V), oracle.bound(A, Bc, idx, m, n, k, N, M, V)
+    assert np.all(np.abs(C - ref) <= w * 2.0 ** -24 * bound + 2.0 ** -149 * w)
+    assert not C[130:150].any() and not C[:, 64:70].any()
