@@ -282,7 +282,10 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
     constexpr int TR = S::TR, TC = S::TC, CR = S::CR;
     typedef typename vec_of<TC>::type cvec;
 
-    __shared__ __align__(16) unsigned char lds[S::LDS_BYTES];
+    // (aligned to 256 bytes: the MFMA tiles of a wave are told apart by an XOR
+    // of address bits 6 and 7)
+    __shared__ __align__(256) unsigned char lds[S::LDS_BYTES];
+    static_assert(STRIDE % 256 == 0 && NRT <= 4, "row pieces of 64 bytes");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tm, tn, split;
