@@ -187,7 +187,10 @@ __device__ __forceinline__ void map_tile(int pid, int nwg, int tiles_m, int tile
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes)
 {
-    // raw buffer, 32-bit dwords; accesses at offsets >= bytes read zero
+    // raw buffer, 32-bit dwords; accesses at offsets >= bytes read zero.  The
+    // offset checked is the sum of the vector and the scalar one, and does not
+    // wrap: a scalar offset past `bytes` (0 included) reads zero too (seen on
+    // gfx950 with every address the alternatives would form inside one buffer)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes,
                                              0x00020000);
 }

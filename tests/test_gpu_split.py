@@ -33,35 +33,88 @@ def inputs(shape, seed, dist):
     return (A, *oracle.compress(Bp, N, M, V))
 
 
-# (m, k, n, N, M, V), stage depth: one and two K steps of 16 rows, three
-# without padding, padded ones, one A slot (KA = 128); m, n and k one short of
-# and one past a tile or a stage, windows of 4 to 128 columns
+# (m, k, n, N, M, V), stage depth: one, two and three K steps of 16 rows, one A
+# slot (KA = 128); m and n one short of and one past a tile; windows of 4 to
+# 128 columns
 STAGES = [
     ((129, 32, 32, 16, 32, 32), 32), ((127, 96, 544, 32, 32, 32), 32), ((257, 224, 480, 4, 8, 32), 32),
-    ((255, 160, 288, 2, 4, 96), 32), ((128, 64, 512, 16, 32, 512), 64), ((385, 320, 1056, 8, 32, 32), 64),
+    ((255, 160, 288, 2, 4, 32), 32), ((128, 64, 512, 16, 32, 512), 64), ((385, 320, 1056, 8, 32, 32), 64),
     ((130, 192, 256, 16, 64, 64), 64), ((300, 512, 544, 4, 32, 32), 128), ((131, 384, 1024, 12, 32, 64), 128),
     ((260, 640, 288, 12, 32, 32), 128), ((129, 256, 512, 16, 128, 128), 128),
 ]
+# a last stage that is not full (k no multiple of the stage depth)
+STAGES += [
+    ((140, 96, 288, 8, 32, 32), 64), ((140, 96, 544, 16, 32, 32), 64), ((129, 32, 320, 16, 32, 64), 64),
+    ((140, 288, 288, 4, 32, 32), 128), ((140, 416, 288, 12, 32, 32), 128), ((130, 160, 544, 3, 32, 32), 128),
+]
+# K steps that are not full: of 20 rows in two (5:8, 20:32), of 24 (24:32, 3:4),
+# 22 and 17 (the second with fewer rows than its lanes' first half), 12 in one,
+# 12 at KA = 128, and 4 (1:32)
+STAGES += [
+    ((140, 160, 544, 5, 8, 32), 32), ((140, 160, 288, 20, 32, 32), 32), ((140, 160, 288, 24, 32, 32), 32),
+    ((140, 160, 288, 3, 4, 32), 32), ((140, 288, 288, 11, 16, 32), 32), ((140, 96, 288, 17, 32, 32), 32),
+    ((140, 160, 288, 12, 32, 32), 32), ((140, 160, 288, 6, 32, 32), 64), ((140, 416, 288, 3, 32, 32), 128),
+    ((140, 416, 288, 1, 32, 32), 128),
+]
 
 
-@pytest.mark.parametrize("splits", [1, 3])
-@pytest.mark.parametrize("tile", TILES)
-@pytest.mark.parametrize("shape,ka", STAGES, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else f"ka{s}")
-def test_stages_exact(shape, ka, tile, splits):
+def stage_tuning(shape, ka, tile, splits):
+    """The tuning that forces a stage; skips where the tile cannot hold it
+    (only 256 rows of A at KA = 128, 96 KB a plane set more than the LDS has)."""
     m, k, n, N, M, V = shape
     tuning = {"TILE": tile, "KA": ka, "SPLITS": splits}
     name = nm.nmspmm_kernel_name(m, n, k, N, M, V, tuning=tuning)
-    if f"<{tile},bv1,ka{ka}," not in name:
-        pytest.skip(f"does not fit: {name}")
+    if tile.startswith("256x256") and ka == 128:
+        pytest.skip("256 rows of A at KA = 128 do not fit in LDS")
+    assert f"<{tile},bv1,ka{ka}," in name, name
+    return tuning
+
+
+def stages(f):
+    f = pytest.mark.parametrize("tile", TILES)(f)
+    ids = lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else f"ka{s}"  # noqa: E731
+    return pytest.mark.parametrize("shape,ka", STAGES, ids=ids)(f)
+
+
+@pytest.mark.parametrize("splits", [1, 3])
+@stages
+def test_stages_exact(shape, ka, tile, splits):
+    """Integers up to 8, exact in the first part alone."""
+    m, k, n, N, M, V = shape
     A, Bc, idx = inputs(shape, 7 + m, "int")
-    C = run(A, Bc, idx, shape, tuning)
-    assert np.array_equal(C.astype(np.float64), oracle.spmm(A, Bc, idx, m, n, k, N, M, V)), name
+    C = run(A, Bc, idx, shape, stage_tuning(shape, ka, tile, splits))
+    assert np.array_equal(C.astype(np.float64), oracle.spmm(A, Bc, idx, m, n, k, N, M, V))
+
+
+@pytest.mark.parametrize("full", ["A", "Bc"])
+@stages
+def test_stages_exact_in_all_three_parts(shape, ka, tile, full):
+    """One operand of integers of 24 bits, which fill all three parts, the other
+    with one power of two per row (A) or column (Bc): every sum is one product,
+    which the three parts of the first give exactly."""
+    m, k, n, N, M, V = shape
+    A, Bc, idx = inputs(shape, 11 + m, "int")
+    w, rng = Bc.shape[0], np.random.default_rng(k + n)
+
+    def wide(x):
+        return ((2 * rng.integers(0, 2, x.shape) - 1) * rng.integers(2 ** 23, 2 ** 24, x.shape)).astype(np.float32)
+
+    if full == "A":
+        A, Bc = wide(A), np.zeros_like(Bc)
+        Bc[rng.integers(0, w, n), np.arange(n)] = 2.0 ** rng.integers(-8, 9, n)
+    else:
+        A, Bc = np.zeros_like(A), wide(Bc)
+        A[np.arange(m), rng.integers(0, k, m)] = 2.0 ** rng.integers(-8, 9, m)
+    C = run(A, Bc, idx, shape, stage_tuning(shape, ka, tile, 1))
+    ref = oracle.spmm(A, Bc, idx, m, n, k, N, M, V)
+    assert ref.any()
+    assert np.array_equal(C.astype(np.float64), ref)
 
 
 @pytest.mark.parametrize("splits", [1, 2])
 def test_operands_without_a_split(splits):
-    """Infinities, NaN, values that round to an infinite bf16 and operands too
-    small for three parts give what fp32 sums give."""
+    """Infinities, NaN, values that round to an infinite bf16 and sums below
+    2^-96 give what fp32 sums give."""
     shape = m, k, n, N, M, V = 300, 256, 576, 16, 32, 32
     A, Bc, idx = inputs(shape, 3, "uniform")
     A[5, 17], A[40, 3], A[41, 200] = np.inf, -np.inf, np.nan
