@@ -143,6 +143,8 @@ const TileInfo TILES[] = {
     {"256x256m32w16", 256, 256, 32, 16, launch_tiled_256x256m32w16, tiled_fits_256x256m32w16},
     {"128x512m32w16", 128, 512, 32, 16, launch_tiled_128x512m32w16, tiled_fits_128x512m32w16},
     {"128x256m32w16", 128, 256, 32, 16, launch_tiled_128x256m32w16, tiled_fits_128x256m32w16},
+    {"128x512m32q", 128, 512, 32, 16, launch_tiled_128x512m32q, tiled_fits_128x512m32q},
+    {"128x256m32q", 128, 256, 32, 16, launch_tiled_128x256m32q, tiled_fits_128x256m32q},
 };
 constexpr int NTILES = sizeof(TILES) / sizeof(TILES[0]);
 
@@ -240,18 +242,25 @@ double occupancy_of_grid(const TileInfo &t, int64_t m, int64_t n)
     return (double)tiles / (double)(rounds * slots);
 }
 
-// Tile-shape preference by problem size where no 16-wave tile is taken
+// Tile-shape preference by problem size where the split kernel is not taken
 // (pick_split), from sweeps on MI355X:
 //  * m <= 128 (when the streaming kernel does not apply): 16- and 64-row
 //    tiles with split-k, which keep enough workgroups in flight to stream Bc;
 //  * m or n below 1024: the 128 x 256 tile with 32 x 32 MFMAs, else the
 //    128 x 128 tile (enough tiles to fill the chip, with split-k);
+//  * otherwise, at N/M <= 1/16 with V a multiple of 32, an fp32 tile of 16
+//    waves where its grid fills the chip in one round (at most 256 tiles, at
+//    least three quarters of the CUs busy): 128 x 512, else 128 x 256.  Four
+//    waves per SIMD hide the A loads of one behind the MFMAs of the others
+//    (m x k x n 4096^3 at 2:32 178 -> 106 us, 1:32 112 -> 103, 8:128 389 ->
+//    110; 2048 x 4096 x 4096 93 -> 88.6, 1536 x 4096 x 4096, two-way split
+//    before, 127 -> 88.5);
 //  * else the 256 x 256 tile for dense-ish levels (N/M >= 1/2) and the
 //    128 x 512 tile with 32 x 32 MFMAs for the sparser ones, unless its grid
 //    would leave more than a quarter of the chip idle in the last wave, where
 //    the 128 x 256 tile with 32 x 32 MFMAs (two workgroups per CU) is tried
 //    first.
-int preferences(int64_t m, int64_t n, int N, int M, const TileInfo **out)
+int preferences(int64_t m, int64_t n, int N, int M, int V, const TileInfo **out)
 {
     int c = 0;
     auto add = [&](const char *name) { out[c++] = tile_by_name(name); };
@@ -262,6 +271,16 @@ int preferences(int64_t m, int64_t n, int N, int M, const TileInfo **out)
     if (m < 1024 || n < 1024) {
         add("128x256m32"); add("128x128"); add("128x512"); add("256x256");
         return c;
+    }
+    if (16 * N <= M && V % 32 == 0) {
+        for (const char *name : {"128x512m32q", "128x256m32q"}) {
+            const TileInfo &t = *tile_by_name(name);
+            const int64_t tiles = ((m + t.BM - 1) / t.BM) * ((n + t.BN - 1) / t.BN);
+            if (tiles <= 256 && occupancy_of_grid(t, m, n) >= 0.75) {
+                add(name);
+                break;
+            }
+        }
     }
     const char *big = 2 * N >= M ? "256x256" : "128x512m32";
     if (occupancy_of_grid(*tile_by_name(big), m, n) < 0.75) add("128x256m32");
@@ -668,7 +687,7 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
     }
 
     const TileInfo *cand[8];
-    int nc = preferences(m, n, N, M, cand);
+    int nc = preferences(m, n, N, M, V, cand);
     if (force_tile) {
         const TileInfo *t = tile_by_name(force_tile);
         if (t) { cand[0] = t; nc = 1; }

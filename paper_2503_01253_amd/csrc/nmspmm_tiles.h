@@ -28,6 +28,8 @@ NMSPMM_DECLARE_TILE(64x1024m32)
 NMSPMM_DECLARE_TILE(256x256m32w16)
 NMSPMM_DECLARE_TILE(128x512m32w16)
 NMSPMM_DECLARE_TILE(128x256m32w16)
+NMSPMM_DECLARE_TILE(128x512m32q)
+NMSPMM_DECLARE_TILE(128x256m32q)
 
 #undef NMSPMM_DECLARE_TILE
 

@@ -406,3 +406,15 @@ def test_dispatch_rules_for_the_split_kernel():
     assert "w16" not in name(4096, 4096, 4096, 2, 32, 32)      # half-empty K steps: the fp32 tiles
     assert "w16" not in name(4096, 4096, 4096, 16, 32, 16)     # V = 16
     assert name(512, 2048, 2048, 12, 32, 32).startswith("nm_skinny_kernel<")
+
+
+def test_dispatch_rules_for_the_sparsest_levels():
+    """Host only.  At N/M <= 1/16 (half-empty K steps in the split kernel) the
+    fp32 tiles of 16 waves where one fills the chip in one round, unsplit."""
+    name = nm.nmspmm_kernel_name
+    for N, M, V in [(2, 32, 32), (1, 16, 32), (4, 64, 64), (8, 128, 128)]:
+        assert name(4096, 4096, 4096, N, M, V) == "nm_tiled_kernel<128x512m32q,bv1,ka128,nq2>,split1"
+        assert name(2048, 4096, 4096, N, M, V) == "nm_tiled_kernel<128x256m32q,bv1,ka128,nq2>,split1"
+    assert name(1536, 4096, 4096, 1, 32, 32) == "nm_tiled_kernel<128x256m32q,bv1,ka128,nq1>,split1"
+    assert "m32q" not in name(4096, 4096, 4096, 2, 32, 16)                                      # V = 16
+    assert "m32q" not in name(1152, 4096, 4096, 2, 32, 32)                                      # 144 of 256 CUs
