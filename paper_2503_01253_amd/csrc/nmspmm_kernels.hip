@@ -590,9 +590,45 @@ bool plan_rowgather(const float *A, const float *Bc, const float *C, int64_t m, 
 // against 337 us, N = M 655 against 626: it is left to TILE.)
 // Stages less than half full of compressed rows (2:32 and below) leave the
 // work to the fp32 instruction's tiles, whose K step is 2 rows.
-struct SplitPick {
+struct SplitTileInfo { const char *name; double t0, t1; };
+const SplitTileInfo SPLIT_WIDE{"128x512m32w16", 2.35, 0.0105}, SPLIT_NARROW{"128x256m32w16", 1.15, 0.0120};
+
+// A stage of one of these tiles: KA columns of A, NQ quads, the number of
+// stages and of K steps over all of k, and the time of a K step.
+struct SplitStage {
     const TileInfo *tile = nullptr;
-    int KA = 0, NQ = 0;
+    int KA = 0, NQ = 0, ks = 0;
+    int64_t stages = 0;
+    double t = 0;
+    double round_us(int64_t splits) const { return (double)((stages + splits - 1) / splits) * ks * t + 8; }
+};
+
+// The stage of KA columns, false where the tile has none for the level.
+bool split_stage(const SplitTileInfo &c, int KA, int64_t k, int N, int M, int V, SplitStage &out)
+{
+    if (KA % M != 0) return false;
+    const TileInfo *tile = tile_by_name(c.name);
+    const int RS = (KA / M) * N, nq = stage_nq(KA, RS), ks = (nq + 3) / 4;
+    if (nq == 0 || 2 * RS <= 16 * ks || !tile_ok(*tile, 1, KA, nq, k, V)) return false;
+    const int64_t gps = KA / M, stages = (k / M + gps - 1) / gps;
+    if (stages > INT32_MAX) return false;
+    // a barrier for every K step of 32 columns costs 5 %: 4096^3 at 16:32 360
+    // us against 345 in stages of two, 1111 x 4192 x 4096 150 against 140
+    out = SplitStage{tile, KA, nq, ks, stages, (c.t0 + c.t1 * KA / ks) * (KA == 32 && ks == 1 ? 1.05 : 1.0)};
+    return true;
+}
+
+// The stage that takes least time over all of k, unsplit.
+bool best_split_stage(const SplitTileInfo &c, int64_t k, int N, int M, int V, SplitStage &out)
+{
+    SplitStage s;
+    for (int KA : {64, 32, 128})
+        if (split_stage(c, KA, k, N, M, V, s) && (!out.tile || s.round_us(1) < out.round_us(1))) out = s;
+    return out.tile != nullptr;
+}
+
+struct SplitPick {
+    SplitStage stage;
     int64_t splits = 1;
     double us = 0;
 };
@@ -602,30 +638,21 @@ bool pick_split(const float *A, const float *Bc, int64_t m, int64_t n, int64_t k
     if (m <= 128 || k == 0 || V % 32 != 0 || k % 4 != 0 || 128 % M != 0 || !aligned(A, 16) || !aligned(Bc, 16))
         return false;
     if (64 * n * 4 >= (int64_t(1) << 31)) return false;   // offsets in a stage of Bc
-    static const struct { const char *name; double t0, t1; } tiles[] = {{"128x512m32w16", 2.35, 0.0105},
-                                                                        {"128x256m32w16", 1.15, 0.0120}};
-    for (const auto &c : tiles) {
-        const TileInfo *tile = tile_by_name(c.name);
-        // a barrier for every K step of 32 columns costs 5 %: 4096^3 at 16:32 360
-        // us against 345 in stages of two, 1111 x 4192 x 4096 150 against 140
+    for (const SplitTileInfo *c : {&SPLIT_WIDE, &SPLIT_NARROW}) {
         for (int KA : {64, 32, 128}) {
-            if (KA % M != 0) continue;
-            const int RS = (KA / M) * N, nq = stage_nq(KA, RS);
-            const int ks = (nq + 3) / 4;
-            if (nq == 0 || 2 * RS <= 16 * ks || !tile_ok(*tile, 1, KA, nq, k, V)) continue;
-            const int64_t gps = KA / M, stages = (k / M + gps - 1) / gps;
-            const int64_t ntiles = ((m + tile->BM - 1) / tile->BM) * ((n + tile->BN - 1) / tile->BN);
-            if (ntiles > (1 << 24) || stages > INT32_MAX) continue;
-            const double t = (c.t0 + c.t1 * KA / ks) * (KA == 32 && ks == 1 ? 1.05 : 1.0);
-            for (int64_t s = 1; s <= std::min<int64_t>(32, stages); ++s) {
+            SplitStage st;
+            if (!split_stage(*c, KA, k, N, M, V, st)) continue;
+            const int64_t ntiles = ((m + st.tile->BM - 1) / st.tile->BM) * ((n + st.tile->BN - 1) / st.tile->BN);
+            if (ntiles > (1 << 24)) continue;
+            for (int64_t s = 1; s <= std::min<int64_t>(32, st.stages); ++s) {
                 const int64_t rounds = (ntiles * s + 255) / 256;
-                double us = rounds * ((double)((stages + s - 1) / s) * ks * t + 8);
+                double us = rounds * st.round_us(s);
                 if (s > 1) us += 5 + (double)m * n * 4 * s / 2e6;
-                if (!out.tile || us < out.us) out = SplitPick{tile, KA, nq, s, us};
+                if (!out.stage.tile || us < out.us) out = SplitPick{st, s, us};
             }
         }
     }
-    return out.tile != nullptr;
+    return out.stage.tile != nullptr;
 }
 
 Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64_t n, int64_t k,
@@ -693,9 +720,9 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
         if (t) { cand[0] = t; nc = 1; }
     }
     if (have_split) {
-        cand[0] = sp.tile;
+        cand[0] = sp.stage.tile;
         nc = 1;
-        ka_deep[0] = sp.KA;
+        ka_deep[0] = sp.stage.KA;
         nkd = 1;
     }
     // first tile shape (in preference order) that some stage depth fits
@@ -748,52 +775,48 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
     // Two column regions where the sparse levels' wide 16-wave tile would
     // need more than one round but the rest fits in one: whole 128 x 512
     // column tiles for one round, then the remaining columns as one round of
-    // the 128 x 256 16-wave tile, a second launch, neither split.  Measured
-    // on MI355X (m x k x n 2048 x 4096 x 11008): at 8:32 316 us, where whole
-    // rounds of one tile take 2 x 194 (128 x 512) or 3 x 133 (128 x 256); at
-    // 4:32 200.
-    if (!force_tile && !ka_force && t.splits < 1 && 4 * N <= M && V % 32 == 0 && m >= 1024 && n >= 1024) {
-        const TileInfo *big = tile_by_name("128x512m32w16"), *rest = tile_by_name("128x256m32w16");
+    // the 128 x 256 16-wave tile, a second launch, neither split.  The split
+    // kernel's tiles in their best stages where it runs and the estimate for
+    // the two rounds is below that of pick_split (at 8:32 and m x k x n 2048 x
+    // 4096 x 11008 316 us, where whole rounds of one tile take 2 x 194 or 3 x
+    // 133); the fp32 tiles at N/M <= 1/16, as in preferences().
+    if (!force_tile && !ka_force && t.splits < 1 && V % 32 == 0 && m >= 1024 && n >= 1024 &&
+        (have_split ? 4 * N <= M : 16 * N <= M)) {
+        const TileInfo *big = tile_by_name(have_split ? "128x512m32w16" : "128x512m32q");
+        const TileInfo *rest = tile_by_name(have_split ? "128x256m32w16" : "128x256m32q");
         const int64_t tm = (m + big->BM - 1) / big->BM;
         const int64_t big_tiles = tm * ((n + big->BN - 1) / big->BN);
         const int64_t cols1 = std::min<int64_t>(256 / tm, n / big->BN) * big->BN;
         const int64_t tn2 = (n - cols1 + rest->BN - 1) / rest->BN;
-        auto fit = [&](const TileInfo *tl, int &bv_out, int &ka_out, int &nq_out) {
-            for (int bv = bv_for(tl->MI, V); bv >= 1; bv /= 2) {
-                if (!aligned(C, 4 * bv)) continue;
-                for (int i = 0; i < nka; ++i) {
-                    const int nq = stage_nq(ka_order[i], (ka_order[i] / M) * N);
-                    if (nq != 0 && tile_ok(*tl, bv, ka_order[i], nq, k, V)) {
-                        bv_out = bv;
-                        ka_out = ka_order[i];
-                        nq_out = nq;
-                        return true;
-                    }
-                }
-            }
-            return false;
-        };
-        int bv1 = 0, ka1 = 0, nq1 = 0, bv2 = 0, ka2 = 0, nq2 = 0;
+        SplitStage s1, s2;
+        bool fit = false;
+        if (have_split) {
+            fit = best_split_stage(SPLIT_WIDE, k, N, M, V, s1) && best_split_stage(SPLIT_NARROW, k, N, M, V, s2) &&
+                  s1.round_us(1) + s2.round_us(1) < sp.us;
+        } else if (tile_ok(*big, 1, 128, stage_nq(128, 128 / M * N), k, V)) {
+            const int64_t all = (k / M + 128 / M - 1) / (128 / M);
+            s1 = s2 = SplitStage{big, 128, stage_nq(128, 128 / M * N), 1, all, 0};
+            fit = tile_ok(*rest, 1, 128, s2.NQ, k, V);
+        }
         // the second round must keep most of the chip busy (R4's keeps 176
         // CUs): a nearly empty one costs a whole round's time
         if (big_tiles > 256 && big_tiles <= 512 && cols1 > 0 && cols1 < n && cols1 % V == 0 && tm * tn2 <= 256 &&
-            tm * tn2 >= 160 &&
-            fit(big, bv1, ka1, nq1) && fit(rest, bv2, ka2, nq2)) {
+            tm * tn2 >= 160 && fit) {
             p.kind = Kind::Tiled;
             p.tile = big;
-            p.BV = bv1;
-            p.KA = ka1;
-            p.NQ = nq1;
-            p.RS = (ka1 / M) * N;
-            p.stages = (int)((groups + ka1 / M - 1) / (ka1 / M));
+            p.BV = 1;
+            p.KA = s1.KA;
+            p.NQ = s1.NQ;
+            p.RS = (s1.KA / M) * N;
+            p.stages = (int)s1.stages;
             p.splits = 1;
             p.tiles_m = (int)tm;
             p.tiles_n = (int)(cols1 / big->BN);
             p.tile2 = rest;
-            p.BV2 = bv2;
-            p.KA2 = ka2;
-            p.NQ2 = nq2;
-            p.stages2 = (int)((groups + ka2 / M - 1) / (ka2 / M));
+            p.BV2 = 1;
+            p.KA2 = s2.KA;
+            p.NQ2 = s2.NQ;
+            p.stages2 = (int)s2.stages;
             p.tiles_n2 = (int)tn2;
             p.col_split = cols1;
             return p;

@@ -418,3 +418,9 @@ def test_dispatch_rules_for_the_sparsest_levels():
     assert name(1536, 4096, 4096, 1, 32, 32) == "nm_tiled_kernel<128x256m32q,bv1,ka128,nq1>,split1"
     assert "m32q" not in name(4096, 4096, 4096, 2, 32, 16)                                      # V = 16
     assert "m32q" not in name(1152, 4096, 4096, 2, 32, 32)                                      # 144 of 256 CUs
+    # two column regions: the same fp32 tiles, not the split kernel half empty
+    for N, nq in [(2, 2), (1, 1)]:
+        assert name(2048, 11008, 4096, N, 32, 32) == (
+            f"nm_tiled_kernel<128x512m32q,bv1,ka128,nq{nq}>,split1"
+            f"+cols8192:nm_tiled_kernel<128x256m32q,bv1,ka128,nq{nq}>,split1")
+    assert "128x512m32w16" in name(2048, 11008, 4096, 3, 32, 32)

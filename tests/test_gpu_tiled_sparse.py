@@ -45,3 +45,16 @@ def test_exact(shape, tile, splits, poison):
                             torch.cuda.current_stream().cuda_stream)
     assert st == 0
     assert np.array_equal(C.cpu().numpy().astype(np.float64), oracle.spmm(A, Bc, idx, m, n, k, N, M, V))
+
+
+@pytest.mark.parametrize("N", [1, 2])
+def test_two_column_regions(N):
+    """28 column tiles of 512 in one round, the other 5120 columns in a second."""
+    m, k, n, M, V = 1152, 160, 19456, 32, 32
+    name = nm.nmspmm_kernel_name(m, n, k, N, M, V)
+    assert name.startswith("nm_tiled_kernel<128x512m32q,") and "+cols14336:nm_tiled_kernel<128x256m32q," in name
+    A, Bp, _ = make_inputs(m, k, n, N, M, V, 3 + N, "int")
+    Bc, idx = oracle.compress(Bp, N, M, V)
+    C = torch.full((m, n), float("nan"), device="cuda")
+    nm.nmspmm_run(*(torch.from_numpy(x).cuda() for x in (A, Bc, idx)), C, m, n, k, N, M, V)
+    assert np.array_equal(C.cpu().numpy().astype(np.float64), oracle.spmm(A, Bc, idx, m, n, k, N, M, V))
