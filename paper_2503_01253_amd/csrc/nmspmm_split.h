@@ -122,6 +122,13 @@ constexpr uint32_t SPLIT_MIN = 2 * 0x08800000u;   // unsigned_bits of 2^-110
 constexpr uint32_t SPLIT_ZERO = 0u - SPLIT_MIN;
 __device__ __forceinline__ uint32_t split_rank(float x) { return unsigned_bits(x) - SPLIT_MIN; }
 
+// min(m, |a|, |b|), as one instruction (fminf would first quieten a and b)
+__device__ __forceinline__ float min_abs(float m, float a, float b)
+{
+    asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(a), "v"(b));
+    return m;
+}
+
 // What follows the stages: whether the split can vouch for every sum of the
 // workgroup's tile, and if not, the tile again on v_mfma_f32_32x32x2_f32, into
 // the same accumulators.  `tiny`: this wave split a non-zero operand below
@@ -133,9 +140,11 @@ __device__ __forceinline__ uint32_t split_rank(float x) { return unsigned_bits(x
 // largest operand: below 2^-26 of a sum that is at least R * 2^-107 * top.  So
 // where an operand was tiny, A and Bc are searched for the largest, and the
 // tile is formed again if a sum is below that.
-// Measured on MI355X: the watch (12 instructions for 8 operands) and this cost
-// 1-4 % (4096^3 at 16:32 338 -> 342 us, 4:32 122 -> 126, 600 x 4096 x 4096 at
-// 16:32 88 -> 92).  4096^3 at 16:32 takes 435 with a few operands of 1e-39 in
+// Measured on MI355X: the watch (12 instructions for 8 operands of A, 4 and a
+// branch for 8 of Bc) and this cost 0-3 % (4096^3 at 16:32 353 -> 355 us, 4:32
+// 125.5 -> 129.5, 600 x 4096 x 4096 at 16:32 90.5 -> 91.4; with the 12 for Bc,
+// too, 357, 129.6 and 94.8; with the 4 for A, too, 130 against 126 where half
+// of A is zero).  4096^3 at 16:32 takes 435 with a few operands of 1e-39 in
 // Bc, 1230 with a NaN in A, 1240 with every sum below 2^-96 (sums formed again
 // one by one from memory: 1720 and 6080; the fp32 tiles: 550).
 //
@@ -329,7 +338,6 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
         }
     };
     uint32_t tiny = 0;   // set once this wave has split a non-zero operand below 2^-110
-    auto watch = [&](uint32_t rank) { tiny |= __any(rank > SPLIT_ZERO) ? 1u : 0u; };
     const int a_dst = ac * STRIDE + 2 * ar, a_swz = (2 * (ac & 3) + (ac >> 2)) << 5;
     auto store_a = [&](int slot) {
         unsigned char *As = lds + (S::TWO_A ? slot * S::A_BYTES : 0);
@@ -342,7 +350,7 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
         for (int t = 0; t < TR; ++t)
 #pragma unroll
             for (int c = 0; c < TC; ++c) rank = max(rank, split_rank(ra[t][c]));
-        watch(rank);
+        tiny |= __any(rank > SPLIT_ZERO) ? 1u : 0u;
 #pragma unroll
         for (int c = 0; c < TC; ++c) {
             // swz(ac + c): ac is a multiple of TC, so ac & 3 plus c stays below 4
@@ -435,10 +443,15 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
             const lds_u8 *at[2];
 #pragma unroll
             for (int x = 0; x < 2; ++x) at[x] = As + (x_area(cur)[(16 * ks + tu + 4 * x) * QBMAX + blk] ^ t_row);
-            uint32_t rank = 0;
+            float least = 1.f;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) rank = max(rank, split_rank(rb[j]));
-            watch(rank);
+            for (int j = 0; j < 8; j += 2) least = min_abs(least, rb[j], rb[j + 1]);
+            if (__any(least < 0x1p-110f)) {   // zero (rare in weights) or tiny
+                uint32_t rank = 0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) rank = max(rank, split_rank(rb[j]));
+                tiny |= __any(rank > SPLIT_ZERO) ? 1u : 0u;
+            }
             u32x4 bp[3];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
