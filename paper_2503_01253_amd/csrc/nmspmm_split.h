@@ -369,6 +369,22 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
         }
     };
 
+    // (debug build) NaN in the places that this thread's next store_a will fill
+    auto poison_a = [&](int slot) {
+        cvec keep[TR];
+        const float nan = __builtin_nanf("");
+#pragma unroll
+        for (int t = 0; t < TR; ++t) {
+            keep[t] = ra[t];
+#pragma unroll
+            for (int c = 0; c < TC; ++c) ra[t][c] = nan;
+        }
+        store_a(slot);
+#pragma unroll
+        for (int t = 0; t < TR; ++t) ra[t] = keep[t];
+        asm volatile("" ::: "memory");
+    };
+
     // ---- D offsets: global -> register -> LDS, entry u * QBMAX + block: where
     // the plane row of the column of A that compressed row u gathers lies ----
     const int gps = KA / M;
@@ -427,15 +443,11 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
     for (int it = 0; it < nst; ++it) {
         const int cur = it & 1;
         const bool next = it + 1 < nst;
-        if constexpr (NMSPMM_POISON_LDS && S::TWO_A) {
-            // the other A slot is free: NaN in the places this thread's store
-            // will fill
-            const float nan = __builtin_nanf("");
-#pragma unroll
-            for (int t = 0; t < TR; ++t)
-#pragma unroll
-                for (int c = 0; c < TC; ++c) ra[t][c] = nan;
-            store_a(cur ^ 1);
+        if constexpr (NMSPMM_POISON_LDS) {
+            // the other slots are free: in the places this thread's stores will
+            // fill, NaN (A) and the place of the stage's last column (offsets)
+            if (S::TWO_A) poison_a(cur ^ 1);
+            if (tid < S::X_ENTRIES) x_area(cur ^ 1)[tid] = (KA - 1) * STRIDE + (swz(KA - 1) << 5);
         }
         const lds_u8 *As = (const lds_u8 *)(lds_void *)lds + (S::TWO_A ? cur * S::A_BYTES : 0);
 #pragma unroll
@@ -495,6 +507,7 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
         }
         // one A slot: every wave must be done reading it
         if constexpr (!S::TWO_A) lds_sync();
+        if constexpr (NMSPMM_POISON_LDS && !S::TWO_A) poison_a(0);
         store_x(cur ^ 1);
         store_a(cur ^ 1);
         lds_sync();

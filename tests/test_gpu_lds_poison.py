@@ -1,9 +1,11 @@
 """Race detection for the LDS pipelines: every kernel family that fills LDS by
 buffer->LDS DMA (the tiled kernel's Bc and offset stages and its A_s slots,
 the pipelined streaming kernel's ring, the register-operand streaming
-kernel's A chunks) run from the library's debug twin, built with
+kernel's A chunks), and the split kernel, which fills its A planes and its
+offsets from registers, run from the library's debug twin, built with
 NMSPMM_POISON_LDS=1.  There every LDS fill first writes NaN (or, for offset
-bytes, an out-of-window value that the readers clamp to a wrong column) into
+bytes, an out-of-window value that the readers clamp to a wrong column; the
+split kernel: the place of the stage's last column) into
 its destination, so a read that runs ahead of a wait or a barrier sees
 poison instead of stale data that may happen to be right.  With small-integer
 inputs every correct result is exact, so any such read fails the comparison.
@@ -69,6 +71,7 @@ TILED_SHAPES = [
     (130, 416, 1024, 4, 32, 64),     # 13 windows: a partial last stage at KA = 64 / 128
     (300, 288, 1088, 16, 32, 32),    # 16:32: the 16-wave tiles' stages of 32 rows at KA = 64, a partial last one
     (130, 192, 1024, 32, 32, 64),    # N = M: stages of 32 rows at KA = 32
+    (140, 416, 544, 12, 32, 32),     # 12:32: three K steps on one A slot at KA = 128, a partial last stage
 ]
 
 
@@ -83,6 +86,22 @@ def test_tiled_kernel_under_poison(shape, tile, ka):
     if f"<{tile}," not in name or (ka and f",ka{ka}," not in name):
         pytest.skip(f"not instantiated for {shape}: {name}")
     name, bad = poisoned_run(shape, tune, seed=3 + ka)
+    assert bad == 0, f"{name}: {bad} outputs differ"
+
+
+@pytest.mark.parametrize("tile", ["256x256m32w16", "128x512m32w16", "128x256m32w16"])
+@pytest.mark.parametrize("shape,ka", [((300, 416, 1088, 8, 32, 32), 64), ((140, 416, 544, 4, 32, 32), 128),
+                                      ((140, 416, 544, 12, 32, 32), 128), ((130, 192, 1024, 32, 32, 64), 32)],
+                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else f"ka{s}")
+def test_split_kernel_runs_over_poison(shape, ka, tile):
+    """Every A slot form (two at KA <= 64 on 128 rows, one otherwise) and every
+    number of K steps; unsplit, so that all stages of k follow one another."""
+    tune = {"TILE": tile, "KA": ka, "SPLITS": 1}
+    if tile.startswith("256x256") and ka == 128:
+        pytest.skip("256 rows of A at KA = 128 do not fit in LDS")
+    name = variant_name(shape, tune)
+    assert f"<{tile},bv1,ka{ka}," in name, name
+    name, bad = poisoned_run(shape, tune, seed=4 + ka)
     assert bad == 0, f"{name}: {bad} outputs differ"
 
 
