@@ -985,6 +985,16 @@ hipError_t launch_main(const Plan &p, const float *A, const float *Bc, const uin
         s.epi = epi;
         // Bc streamed past L2: at least 16 MB, four XCDs' worth
         s.stream_b = (k / M) * N * n * 4 >= (int64_t(16) << 20) ? 1 : 0;
+        // Column tiles in runs on the XCDs: over 168 shapes of 8 and 16 rows
+        // (MI355X, against round-robin) faster only with k split over a
+        // multiple of 16 tiles of a Bc of 32 MB or more (16 x 8192 x 8192 at
+        // 4:32 13.7 -> 13.2 us, 16 x 11008 x 8192 17.0 -> 16.4, 8 x 8192 x
+        // 2048 at 16:32 13.3 -> 12.8; the mean over these 0.7 % faster).
+        // Elsewhere slower: 24 and 40 tiles 3-10 % (16 x 8192 x 3072 at 16:32
+        // 24.2 -> 26.2 us), 1 x 3264 x 1568 at 20:32 9.1 -> 14.9, one split on
+        // small k 1-5 % (8 x 2048 x 4096 at 4:32 6.4 -> 6.7).
+        s.xcd_runs = p.tiles_m == 1 && p.splits > 1 && p.tiles_n % 16 == 0 &&
+                     (k / M) * N * n * 4 >= (int64_t(32) << 20) ? 1 : 0;
         return launch_skinny(p.RT, p.BV, p.QPW, p.COLS, s, stream);
     }
     if (p.kind == Kind::Gather) {

@@ -22,6 +22,9 @@ struct SkinnyArgs {
     int cw;              // windows per staged chunk of A: cw * M <= skinny_chunk_cols(RT)
     Epilogue epi;        // applied by the stores when splits == 1
     int stream_b;        // 1: Bc loads with the non-temporal hint (Bc much larger than L2)
+    // 1: consecutive column tiles, whose Bc rows are neighbours in memory, on
+    // one XCD (needs tiles_m == 1 and tiles_n * splits a multiple of 8)
+    int xcd_runs = 0;
 };
 
 int skinny_rows(int RT);        // rows of C per workgroup with RT row tiles

@@ -96,18 +96,9 @@ __global__ __launch_bounds__(SK_NT) void nm_skinny_kernel(SkinnyArgs p)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, kq = lane >> 4;
     const int tiles_n = p.tiles_n;
-    // Workgroups are dispatched round-robin over the 8 XCDs.  With one row
-    // tile, renumber them so that consecutive column tiles, whose Bc rows are
-    // neighbours in memory, run on one XCD: reading 512-byte pieces of 32 KB
-    // rows takes 6.0 us that way and 8.7 us with neighbours on different XCDs
-    // (33.5 MB); 16 x 8192 x 8192 at 4:32 13.7 -> 13.2 us.  With several row
-    // tiles the round-robin order stays: each XCD then reads fewer columns of
-    // Bc (128 x 2048 x 2048 at 16:32 13.8 us against 16.5 renumbered).
+    // Workgroups are dispatched round-robin over the 8 XCDs; see SkinnyArgs.
     int pid = blockIdx.x;
-    if (p.tiles_m == 1) {
-        const int nwg = gridDim.x, xcd = pid % 8, local = pid / 8, full = nwg / 8, rem = nwg % 8;
-        pid = xcd < rem ? xcd * (full + 1) + local : rem * (full + 1) + (xcd - rem) * full + local;
-    }
+    if (p.xcd_runs) pid = pid % 8 * (tiles_n * p.splits / 8) + pid / 8;
     const int tile = pid % (p.tiles_m * tiles_n);
     const int split = pid / (p.tiles_m * tiles_n);
     const int tm = tile / tiles_n, tn = tile % tiles_n;
