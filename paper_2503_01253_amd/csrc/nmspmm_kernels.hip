@@ -305,18 +305,6 @@ bool prefer_streaming(int64_t m, int64_t k, int N, int M)
     return m <= 128 || (m <= 1024 && m * w <= (int64_t(1) << 20));
 }
 
-// Time expected of the streaming kernels above 128 rows, from measured rates:
-// 60 TFLOP/s from 512 rows on at 12:32 and 16:32 (512 x 2048 x 2048 at 12:32
-// 27.5 us, 1024 x 2048 x 2048 52 us), 72 from 1024 rows on at N/M <= 1/4
-// (1024 x 4096 x 4096 at 4:32 60 us), and less on fewer rows (m x k x n: 300 x
-// 4096 x 4096 41 at 16:32 and 36 at 8:32, 600 x 4096 x 11008 at 4:32 57).
-double streaming_us(int64_t m, int64_t n, int64_t k, int N, int M)
-{
-    const bool sparse = 4 * N <= M;
-    const double full = sparse ? 72e6 : 60e6, part = std::sqrt((double)m / (sparse ? 1024 : 512));
-    return 5 + 2.0 * m * n * ((k / M) * N) / (full * std::min(1.0, part));
-}
-
 // Overrides of the dispatch rules, for tuning sweeps and the forced-variant
 // tests only.  They come from the tuning string of the *_tuned entry points
 // ("KEY=VALUE" pairs separated by commas); the default entry points use none
@@ -655,6 +643,27 @@ bool pick_split(const float *A, const float *Bc, int64_t m, int64_t n, int64_t k
     return out.stage.tile != nullptr;
 }
 
+// Time expected of the streaming kernels above 128 rows.  The pipelined one on
+// 32 x 256 tiles (`pipelined`: its plan), fitted to seven products of 200 to
+// 1024 rows at 2:8 and 6:32 within 10 %: 8 us + rounds * (1.5 us + 45.5 ns *
+// w) (361 x 2144 x 8608 at 6:32 47.6 us, where the split kernel took 58.7;
+// 1024 x 4096 x 2048 at 8:32 51.8 against 61.5).  Else from rates: 60 TFLOP/s from
+// 512 rows on at 12:32 and 16:32 (512 x 2048 x 2048 at 12:32 27.5 us, 1024 x
+// 2048 x 2048 52 us), 72 from 1024 rows on at N/M <= 1/4 (1024 x 4096 x 4096
+// at 4:32 60 us), and less on fewer rows (m x k x n: 300 x 4096 x 4096 41 at
+// 16:32 and 36 at 8:32, 600 x 4096 x 11008 at 4:32 57).
+double streaming_us(int64_t m, int64_t n, int64_t k, int N, int M, const Plan *pipelined)
+{
+    const int64_t w = (k / M) * N;
+    if (pipelined && pipelined->RT == 2 && pipelined->COLS == 256 && pipelined->splits == 1) {
+        const int64_t rounds = ((int64_t)pipelined->tiles_m * pipelined->tiles_n + 255) / 256;
+        return 8 + rounds * (1.5 + 0.0455 * w);
+    }
+    const bool sparse = 4 * N <= M;
+    const double full = sparse ? 72e6 : 60e6, part = std::sqrt((double)m / (sparse ? 1024 : 512));
+    return 5 + 2.0 * m * n * w / (full * std::min(1.0, part));
+}
+
 Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64_t n, int64_t k,
                int N, int M, int V, const Tuning &t)
 {
@@ -662,9 +671,17 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
     if (m == 0 || n == 0) return p;
     const char *force_tile = t.tile_or_null();
     SplitPick sp;
-    const bool have_split = !force_tile && t.ka == 0 && t.splits < 1 && pick_split(A, Bc, m, n, k, N, M, V, sp);
-    const bool want_skinny = force_tile ? std::strcmp(force_tile, "skinny") == 0
-                                        : prefer_streaming(m, k, N, M) && !(have_split && sp.us < streaming_us(m, n, k, N, M));
+    bool have_split = false;
+    bool want_skinny = force_tile ? std::strcmp(force_tile, "skinny") == 0 : prefer_streaming(m, k, N, M);
+    if (!force_tile && t.ka == 0 && t.splits < 1 && m > 128) {
+        // (the split kernel takes 9 us at least: its estimate, 2 us of host
+        // time, is not formed for the products that stream faster than that)
+        Plan q;
+        const bool pipelined = want_skinny && plan_stream(A, Bc, C, m, n, k, N, M, V, false, t, q);
+        const double stream = want_skinny ? streaming_us(m, n, k, N, M, pipelined ? &q : nullptr) : HUGE_VAL;
+        have_split = stream > 9 && pick_split(A, Bc, m, n, k, N, M, V, sp);
+        want_skinny = want_skinny && !(have_split && sp.us < stream);
+    }
     if (want_skinny) {
         if (t.rg != 0 && plan_rowgather(A, Bc, C, m, n, k, N, M, V, t.rg == 1, t, p)) return p;
         // the PS override (tuning sweeps and tests): 0 never takes the
@@ -788,20 +805,21 @@ Plan make_plan(const float *A, const float *Bc, const float *C, int64_t m, int64
         const int64_t big_tiles = tm * ((n + big->BN - 1) / big->BN);
         const int64_t cols1 = std::min<int64_t>(256 / tm, n / big->BN) * big->BN;
         const int64_t tn2 = (n - cols1 + rest->BN - 1) / rest->BN;
+        // the second round must keep most of the chip busy (R4's keeps 176
+        // CUs): a nearly empty one costs a whole round's time
+        const bool two_rounds = big_tiles > 256 && big_tiles <= 512 && cols1 > 0 && cols1 < n && cols1 % V == 0 &&
+                                tm * tn2 <= 256 && tm * tn2 >= 160;
         SplitStage s1, s2;
         bool fit = false;
-        if (have_split) {
+        if (two_rounds && have_split) {
             fit = best_split_stage(SPLIT_WIDE, k, N, M, V, s1) && best_split_stage(SPLIT_NARROW, k, N, M, V, s2) &&
                   s1.round_us(1) + s2.round_us(1) < sp.us;
-        } else if (tile_ok(*big, 1, 128, stage_nq(128, 128 / M * N), k, V)) {
+        } else if (two_rounds && tile_ok(*big, 1, 128, stage_nq(128, 128 / M * N), k, V)) {
             const int64_t all = (k / M + 128 / M - 1) / (128 / M);
             s1 = s2 = SplitStage{big, 128, stage_nq(128, 128 / M * N), 1, all, 0};
             fit = tile_ok(*rest, 1, 128, s2.NQ, k, V);
         }
-        // the second round must keep most of the chip busy (R4's keeps 176
-        // CUs): a nearly empty one costs a whole round's time
-        if (big_tiles > 256 && big_tiles <= 512 && cols1 > 0 && cols1 < n && cols1 % V == 0 && tm * tn2 <= 256 &&
-            tm * tn2 >= 160 && fit) {
+        if (fit) {
             p.kind = Kind::Tiled;
             p.tile = big;
             p.BV = 1;

@@ -424,3 +424,13 @@ def test_dispatch_rules_for_the_sparsest_levels():
             f"nm_tiled_kernel<128x512m32q,bv1,ka128,nq{nq}>,split1"
             f"+cols8192:nm_tiled_kernel<128x256m32q,bv1,ka128,nq{nq}>,split1")
     assert "128x512m32w16" in name(2048, 11008, 4096, 3, 32, 32)
+
+
+def test_dispatch_between_the_streaming_and_the_split_kernel():
+    """Host only.  The pipelined streaming kernel on 32 x 256 tiles by its own
+    estimate, where rates had it slower than it is."""
+    name = nm.nmspmm_kernel_name
+    for m, n, k, N, M, V in [(1024, 2048, 4096, 8, 32, 32), (361, 8608, 2144, 6, 32, 32), (637, 6400, 832, 2, 8, 128)]:
+        assert name(m, n, k, N, M, V).startswith("nm_stream_kernel<r32,c256,"), (m, n, k)
+    for m, n, k, N, M, V in [(986, 3840, 3936, 2, 8, 64), (488, 5248, 2880, 2, 8, 128), (300, 4096, 4096, 16, 32, 32)]:
+        assert "w16" in name(m, n, k, N, M, V), (m, n, k)
