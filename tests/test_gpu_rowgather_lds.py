@@ -66,6 +66,28 @@ def test_rows_past_w_gather_zeros(m):
     assert np.array_equal(C.astype(np.float64), oracle.spmm(A, Bc, idx, m, n, k, N, M, V))
 
 
+@pytest.mark.parametrize("shape", [(4, 4096, 6144, 16, 32, 32), (3, 10496, 6784, 4, 16, 128), (6, 3168, 6720, 2, 8, 32)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_error_beside_the_streaming_kernel(shape):
+    """Against fp64 no more than a quarter above the streaming kernel, which
+    these shapes split 2 to 4 ways (2-norms; measured 0.99 to 1.15 of it; one
+    set of sums a wave had 1.7 to 2.1)."""
+    m, k, n, N, M, V = shape
+    assert nm.nmspmm_kernel_name(m, n, k, N, M, V).startswith("nm_rowgather_kernel<r16,")
+    A, Bp, _ = make_inputs(m, k, n, N, M, V, 21, "uniform")
+    Bc, idx = oracle.compress(Bp, N, M, V)
+    ref = oracle.spmm(A, Bc, idx, m, n, k, N, M, V)
+    dA, dBc, didx = (torch.from_numpy(x).cuda() for x in (A, Bc, idx))
+
+    def err(tuning):
+        C = torch.full((m, n), float("nan"), device="cuda")
+        nm.nmspmm_run(dA, dBc, didx, C, m, n, k, N, M, V, tuning=tuning)
+        return np.linalg.norm(C.cpu().numpy() - ref) / np.linalg.norm(ref)
+
+    staged, streaming = err(None), err({"TILE": "skinny", "RG": 0, "PS": 0})
+    assert staged <= 1.25 * streaming, (staged, streaming)
+
+
 def test_default_dispatch():
     name = nm.nmspmm_kernel_name
     assert name(8, 8192, 4096, 4, 32, 32).startswith("nm_rowgather_kernel<r16,")     # A fits, 256 strips
