@@ -208,8 +208,12 @@ def _call(torch, at, fn, *args):
 
 def _raw_stream(torch, at, stream):
     """The hipStream_t of `stream`, or of torch's current stream on device
-    `at` (read without building a Stream object, which takes 1 us)."""
-    return torch._C._cuda_getCurrentRawStream(at) if stream is None else stream.cuda_stream
+    `at`: from torch's own accessor, which builds no Stream object (1 us),
+    where this torch has it."""
+    if stream is not None:
+        return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(at) if raw else torch.cuda.current_stream(at).cuda_stream
 
 
 def nmspmm_run(A, Bc, idx, C, m: int, n: int, k: int, N: int, M: int, V: int, stream=None, tuning=None):

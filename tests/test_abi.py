@@ -434,3 +434,15 @@ def test_dispatch_between_the_streaming_and_the_split_kernel():
         assert name(m, n, k, N, M, V).startswith("nm_stream_kernel<r32,c256,"), (m, n, k)
     for m, n, k, N, M, V in [(986, 3840, 3936, 2, 8, 64), (488, 5248, 2880, 2, 8, 128), (300, 4096, 4096, 16, 32, 32)]:
         assert "w16" in name(m, n, k, N, M, V), (m, n, k)
+
+
+def test_stream_handle_without_torchs_private_accessor():
+    """The binding's stream handle comes from the public interface where torch
+    has no _cuda_getCurrentRawStream."""
+    from types import SimpleNamespace as NS
+
+    from paper_2503_01253_amd.binding import _raw_stream
+    cuda = NS(current_stream=lambda at: NS(cuda_stream=100 + at))
+    assert _raw_stream(NS(_C=NS(), cuda=cuda), 3, None) == 103
+    assert _raw_stream(NS(_C=NS(_cuda_getCurrentRawStream=lambda at: 200 + at), cuda=cuda), 3, None) == 203
+    assert _raw_stream(NS(_C=NS(), cuda=cuda), 3, NS(cuda_stream=7)) == 7
