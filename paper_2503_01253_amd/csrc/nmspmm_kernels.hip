@@ -631,8 +631,10 @@ bool pick_split(const float *A, const float *Bc, int64_t m, int64_t n, int64_t k
             SplitStage st;
             if (!split_stage(*c, KA, k, N, M, V, st)) continue;
             const int64_t ntiles = ((m + st.tile->BM - 1) / st.tile->BM) * ((n + st.tile->BN - 1) / st.tile->BN);
-            if (ntiles > (1 << 24)) continue;
             for (int64_t s = 1; s <= std::min<int64_t>(32, st.stages); ++s) {
+                // a launch has less than 2^32 threads, 1024 a workgroup (the
+                // 8-wave tiles reach twice as many)
+                if (ntiles * s >= (1 << 22)) break;
                 const int64_t rounds = (ntiles * s + 255) / 256;
                 double us = rounds * st.round_us(s);
                 if (s > 1) us += 5 + (double)m * n * 4 * s / 2e6;

@@ -446,3 +446,11 @@ def test_stream_handle_without_torchs_private_accessor():
     assert _raw_stream(NS(_C=NS(), cuda=cuda), 3, None) == 103
     assert _raw_stream(NS(_C=NS(_cuda_getCurrentRawStream=lambda at: 200 + at), cuda=cuda), 3, None) == 203
     assert _raw_stream(NS(_C=NS(), cuda=cuda), 3, NS(cuda_stream=7)) == 7
+
+
+def test_split_kernel_stays_within_a_launch():
+    """Host only.  2^29 rows of 32 columns are 2^22 tiles: 2^32 threads of the
+    16-wave tiles, more than a launch has, but 2^31 of the 8-wave ones."""
+    name = nm.nmspmm_kernel_name
+    assert "w16" in name((1 << 29) - 128, 32, 32, 16, 32, 32)
+    assert name(1 << 29, 32, 32, 16, 32, 32).startswith("nm_tiled_kernel<128x256m32,")
