@@ -525,25 +525,34 @@ bool plan_stream(const float *A, const float *Bc, const float *C, int64_t m, int
 // Row-gather kernel: up to 32 rows, one launch, every output written once.
 // By default for at most 4 rows where its 32-column strips alone fill the
 // chip: each quad then gathers at most 4 lines of A, and the single launch
-// beats the streaming kernel's zero fill and split-k atomics.  Measured on
-// MI355X (graph replay, against the register-operand streaming kernel with
-// split-k): k = n = 8192 at 4:32, V = 64: 1 row 13.0 -> 10.9 us, 2 rows 13.1
-// -> 11.3, 4 rows 13.2 -> 12.2; 4 x 11008 x 4096 at 8:32 27.4 -> 21.9.  From
-// 8 rows on the gathered lines cost more than the launch and atomics they
-// save (8 rows 13.4 against 13.9 us, 16 rows 14.2 against 18.0), and with
-// fewer strips the grid does not fill the chip (1 x 4096 x 4096 at 8:32,
-// V = 32: 9.9 against 10.2).  `force` (tuning sweeps and tests) takes it
-// wherever it can run.
+// beats the streaming kernel's zero fill and split-k atomics (MI355X, graph
+// replay, k = n = 8192 at 4:32, V = 64: 1 row 13.0 -> 10.9 us, 2 rows 13.1 ->
+// 11.3, 4 rows 13.2 -> 12.2; 4 x 11008 x 4096 at 8:32 27.4 -> 21.9).
+//
+// Up to 16 rows also where A and a strip's offsets fit in LDS (`staged`).  720
+// products of 1 to 16 rows (k 512 to 8192, n 1024 to 16384, 4:32 to 16:32, V =
+// 32) took 0.83 of the streaming kernels' time where the rule holds.  Outside
+// it, with the other conditions holding (geometric means):
+//  * rows against k: 8 to 16 rows at k <= 1024 0.98, at most 1.13 (8 x 1024 x
+//    11008 at 16:32 11.5 against 10.1 us), at k = 2048 0.87;
+//  * rows against w: 12 and 16 rows at w = 256 1.01 (at w = 512 0.92);
+//  * strips: above w = 512 64 strips 1.02, up to 1.83 (4 x 8192 x 2048 at 16:32
+//    23.0 against 12.6), 128 strips 0.97, up to 1.45, but 192 strips 0.63; at
+//    w <= 512 64 and 128 strips 0.86;
+//  * more than one round of strips at one workgroup per CU or two, k <= 2048
+//    and w < 1024: 1.16 (16 x 2048 x 11008 at 8:32 14.5 against 11.3), otherwise
+//    0.86; above 4 rows 512 strips 1.11 (8 x 4096 x 16384 at 16:32 34.3 against
+//    28.7), 272 and 344 strips 0.77.
+// `force` (tuning sweeps and tests) takes it wherever it can run.
 bool plan_rowgather(const float *A, const float *Bc, const float *C, int64_t m, int64_t n, int64_t k, int N,
                     int M, int V, bool force, const Tuning &t, Plan &p)
 {
     if (m > 32 || k == 0 || !aligned(A, 4) || !aligned(Bc, 16) || !aligned(C, 4)) return false;
     const int64_t strips = n / 32, w = k / M * N;
-    const int kb = rowgather_lds_kb(A, m, k, N, M);
+    const int kb = rowgather_lds_kb(A, m, n, k, N, M);
     const bool staged = kb && (m <= 4 || k > 1024) && (m <= 8 || w >= 512) &&
                         (strips >= 192 || (strips >= 64 && w <= 512)) &&
-                        (strips <= 256 || (w >= 448 && (kb == 48 || k > 2048 || w >= 1024) &&
-                                           (kb < 150 || w <= 2048 || strips % 256 == 0 || strips % 256 >= 48)));
+                        (strips <= 256 || kb == 48 || k > 2048 || w >= 1024) && (m <= 4 || strips < 512);
     if (!force && !staged && (m > 4 || strips < 256)) return false;
     RowGatherCfg c{m <= 16 ? 1 : 2, 2, 8, 4};
     if (t.rgct) c.CT = t.rgct;

@@ -35,9 +35,10 @@ bool rowgather_has(const RowGatherCfg &c);
 bool rowgather_fits(const RowGatherCfg &c, int64_t m, int64_t n, int64_t k, int N, int M, int V);
 
 // KB of LDS of the kernel that stages all of A and a strip's offsets there
-// ({1, 2, 8, 4}, up to 16 rows, taken wherever it can be): 48, 80 or 150; 0
-// where they do not fit or A cannot be moved in 16-byte pieces.
-int rowgather_lds_kb(const float *A, int64_t m, int64_t k, int N, int M);
+// ({1, 2, 8, 4}, up to 16 rows): 48, 80 or 150; 0 where that kernel is not
+// taken: they do not fit, A cannot be moved in 16-byte pieces, or the strips
+// take more than one round on fewer than 448 compressed rows.
+int rowgather_lds_kb(const float *A, int64_t m, int64_t n, int64_t k, int N, int M);
 
 // One launch, no workspace: every output written once.
 hipError_t launch_rowgather(const RowGatherCfg &c, const RowGatherArgs &a, hipStream_t stream);

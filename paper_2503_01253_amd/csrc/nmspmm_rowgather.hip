@@ -419,10 +419,7 @@ hipError_t launch_cfg(const RowGatherArgs &a, hipStream_t stream)
     const unsigned strips = (unsigned)(a.n / (16 * CT));
     const uint32_t magic = a.N == 1 ? 0u : (uint32_t)(((uint64_t(1) << 32) + (uint64_t)a.N - 1) / (uint64_t)a.N);
     if constexpr (RT == 1 && CT == 2 && NW == 8 && D == 4) {
-        // on more than one round of strips the staging pays from about w = 450 on: 2 x
-        // 1888 x 9792 at 8:32 (w = 472) 10.7 -> 9.6 us, but 2 x 1248 x 8736 at 4:32
-        // (w = 156) 5.8 -> 6.5 and 3 x 3328 x 9952 (w = 416) 8.4 -> 8.8
-        const int kb = strips <= 256 || w >= 448 ? rowgather_lds_kb(a.A, a.m, a.k, a.N, a.M) : 0;
+        const int kb = rowgather_lds_kb(a.A, a.m, a.n, a.k, a.N, a.M);
         if (kb) {
             // (m = 2: 9.7 us in either form, m = 4: 10.4 by MFMA, 11.8 by FMA, 8192 x 8192 at 4:32)
             const bool one = a.m == 1;
@@ -450,10 +447,15 @@ hipError_t launch_cfg(const RowGatherArgs &a, hipStream_t stream)
 
 }  // namespace
 
-int rowgather_lds_kb(const float *A, int64_t m, int64_t k, int N, int M)
+int rowgather_lds_kb(const float *A, int64_t m, int64_t n, int64_t k, int N, int M)
 {
     if (m > 16 || k % 4 != 0 || reinterpret_cast<uintptr_t>(A) % 16 != 0) return 0;
-    const int64_t w = k / M * N, bytes = m * rg_stride(k) * 4 + (w + 7) / 8 * 32;
+    const int64_t w = k / M * N;
+    // on more than one round of strips the staging pays from about w = 450 on: 2 x
+    // 1888 x 9792 at 8:32 (w = 472) 10.7 -> 9.6 us, but 2 x 1248 x 8736 at 4:32
+    // (w = 156) 5.8 -> 6.5 and 3 x 3328 x 9952 (w = 416) 8.4 -> 8.8
+    if (n / 32 > 256 && w < 448) return 0;
+    const int64_t bytes = m * rg_stride(k) * 4 + (w + 7) / 8 * 32;
     for (int kb : {48, 80, 150})   // three, two and one workgroup per CU
         if (bytes <= kb * 1024) return kb;
     return 0;

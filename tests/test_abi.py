@@ -454,3 +454,17 @@ def test_split_kernel_stays_within_a_launch():
     name = nm.nmspmm_kernel_name
     assert "w16" in name((1 << 29) - 128, 32, 32, 16, 32, 32)
     assert name(1 << 29, 32, 32, 16, 32, 32).startswith("nm_tiled_kernel<128x256m32,")
+
+
+def test_dispatch_rules_for_decode_batches():
+    """Host only.  The staged row-gather kernel on both sides of its lines, each
+    with the other conditions holding."""
+    name = nm.nmspmm_kernel_name
+    rg, sk = "nm_rowgather_kernel<r16,c32,w8,d4>", "nm_skinny_kernel<"
+    for m, n, k, N, want in [
+            (8, 8192, 2048, 8, rg), (8, 8192, 1024, 16, sk), (4, 4096, 512, 8, rg),    # rows against k
+            (12, 8192, 2048, 8, rg), (12, 8192, 2048, 4, sk),                          # rows against w
+            (1, 6144, 4096, 8, rg), (1, 4096, 4096, 8, sk), (1, 2048, 2048, 8, rg), (1, 1024, 2048, 8, sk),   # strips
+            (16, 8704, 2048, 16, rg), (16, 8704, 2048, 8, sk), (8, 11008, 4096, 8, rg),    # a second round
+            (8, 16384, 4096, 16, sk), (4, 16384, 4096, 16, rg)]:                       # 512 strips
+        assert name(m, n, k, N, 32, 32).startswith(want), (m, n, k, N, name(m, n, k, N, 32, 32))
