@@ -141,10 +141,10 @@ __device__ __forceinline__ float min_abs(float m, float a, float b)
 // where an operand was tiny, A and Bc are searched for the largest, and the
 // tile is formed again if a sum is below that.
 // Measured on MI355X: the watch (12 instructions for 8 operands of A, 4 and a
-// branch for 8 of Bc) and this cost 0-3 % (4096^3 at 16:32 353 -> 355 us, 4:32
-// 125.5 -> 129.5, 600 x 4096 x 4096 at 16:32 90.5 -> 91.4; with the 12 for Bc,
-// too, 357, 129.6 and 94.8; with the 4 for A, too, 130 against 126 where half
-// of A is zero).  4096^3 at 16:32 takes 435 with a few operands of 1e-39 in
+// branch for 8 of Bc) and this cost 0-4 % (4096^3 at 16:32 337.6 -> 337.1 us,
+// 8:32 194.4 -> 193.7, 4:32 123.2 -> 128.1, 600 x 4096 x 4096 at 16:32 90.5 ->
+// 91.4; with the 12 for Bc, too, the last 94.8; with the 4 for A, too, 3 %
+// more at 4:32 where half of A is zero; A's after its stores no difference).  4096^3 at 16:32 takes 435 with a few operands of 1e-39 in
 // Bc, 1230 with a NaN in A, 1240 with every sum below 2^-96 (sums formed again
 // one by one from memory: 1720 and 6080; the fp32 tiles: 550).
 //
@@ -505,10 +505,10 @@ __global__ __launch_bounds__(T::NT) void nm_tiled_split_kernel(TiledArgs p)
                 mma(0, 0);
             }
         }
+        store_x(cur ^ 1);
         // one A slot: every wave must be done reading it
         if constexpr (!S::TWO_A) lds_sync();
         if constexpr (NMSPMM_POISON_LDS && !S::TWO_A) poison_a(0);
-        store_x(cur ^ 1);
         store_a(cur ^ 1);
         lds_sync();
     }
