@@ -1,8 +1,9 @@
 """Race detection for the LDS pipelines: every kernel family that fills LDS by
 buffer->LDS DMA (the tiled kernel's Bc and offset stages and its A_s slots,
 the pipelined streaming kernel's ring, the register-operand streaming
-kernel's A chunks), and the split kernel, which fills its A planes and its
-offsets from registers, run from the library's debug twin, built with
+kernel's A chunks, the row-gather kernel's copy of A), and the split kernel,
+which fills its A planes and its offsets from registers, run from the
+library's debug twin, built with
 NMSPMM_POISON_LDS=1.  There every LDS fill first writes NaN (or, for offset
 bytes, an out-of-window value that the readers clamp to a wrong column; the
 split kernel: the place of the stage's last column) into
@@ -134,6 +135,15 @@ def test_skinny_kernel_under_poison(shape, rt, cols, qpw, splits):
     if not name.startswith(f"nm_skinny_kernel<c{cols},") or f"qpw{qpw}" not in name:
         pytest.skip(f"not instantiated for {shape}: {name}")
     name, bad = poisoned_run(shape, tune, seed=9 + cols)
+    assert bad == 0, f"{name}: {bad} outputs differ"
+
+
+@pytest.mark.parametrize("shape", [(1, 8192, 512, 16, 32, 32), (4, 8192, 256, 4, 32, 32), (16, 2048, 288, 8, 32, 96),
+                                   (15, 260, 256, 13, 20, 64)], ids=lambda s: "x".join(map(str, s)))
+def test_rowgather_kernel_with_a_in_lds_under_poison(shape):
+    """Shapes whose A fits in LDS, so that the kernel of this name copies it."""
+    name, bad = poisoned_run(shape, {"TILE": "skinny", "RG": 1}, seed=3)
+    assert name.startswith("nm_rowgather_kernel<r16,c32,w8,d4>")
     assert bad == 0, f"{name}: {bad} outputs differ"
 
 
